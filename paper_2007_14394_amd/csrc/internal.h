@@ -171,6 +171,9 @@ hipError_t launch_sample(const SampleArgs &a, hipStream_t stream);
 hipError_t launch_pack_quads(const float *grid, int n0, int n1, int n2, bool half, void *quad,
                              hipStream_t stream);
 hipError_t launch_fill_u8(uint8_t *dst, uint8_t value, int64_t n, hipStream_t stream);
+// n0 floats s0 -> d0 and n1 floats s1 -> d1 (either count may be 0, its pointers then unused).
+hipError_t launch_copy_pair(float *d0, const float *s0, int64_t n0, float *d1, const float *s1,
+                            int64_t n1, hipStream_t stream);
 
 }  // namespace sdfddgi
 

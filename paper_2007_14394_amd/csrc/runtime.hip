@@ -1241,14 +1241,9 @@ sdfddgi_status sdfddgi_sample_irradiance(sdfddgi_ctx *c, const float *points,
 sdfddgi_status sdfddgi_get_maps(sdfddgi_ctx *c, float *irr, float *depth) {
     sdfddgi_status st = check_ctx(c);
     if (st != SDFDDGI_OK) return st;
-    if (irr)
-        TRY_HIP(c, hipMemcpyAsync(irr, c->irr[c->cur], c->irr_floats * sizeof(float),
-                                  hipMemcpyDeviceToDevice, c->stream),
-                "copying irradiance atlas");
-    if (depth)
-        TRY_HIP(c, hipMemcpyAsync(depth, c->depth[c->cur], c->depth_floats * sizeof(float),
-                                  hipMemcpyDeviceToDevice, c->stream),
-                "copying depth atlas");
+    TRY_HIP(c, launch_copy_pair(irr, c->irr[c->cur], irr ? c->irr_floats : 0, depth,
+                                c->depth[c->cur], depth ? c->depth_floats : 0, c->stream),
+            "copying the atlases");
     return SDFDDGI_OK;
 }
 
@@ -2761,13 +2756,12 @@ sdfddgi_status sdfddgi_batch_get_maps(sdfddgi_batch *b, int32_t scene, float *ir
     b->serialize_next = true;
     const BatchScene &d = b->host_scenes[scene];
     const size_t ti = 10 * 10 * 3, td = 18 * 18 * 2;
-    hipError_t e = hipSuccess;
-    if (irr)
-        e = hipMemcpyAsync(irr, b->irr[b->cur] + (size_t)d.probe_base * ti,
-                           (size_t)d.P * ti * sizeof(float), hipMemcpyDeviceToDevice, b->stream);
-    if (e == hipSuccess && depth)
-        e = hipMemcpyAsync(depth, b->depth[b->cur] + (size_t)d.probe_base * td,
-                           (size_t)d.P * td * sizeof(float), hipMemcpyDeviceToDevice, b->stream);
+    hipError_t e = hipSetDevice(b->device);
+    if (e != hipSuccess) return lhip_fail(e, "hipSetDevice");
+    e = launch_copy_pair(irr, b->irr[b->cur] + (size_t)d.probe_base * ti,
+                         irr ? d.P * (int64_t)ti : 0, depth,
+                         b->depth[b->cur] + (size_t)d.probe_base * td,
+                         depth ? d.P * (int64_t)td : 0, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return lhip_fail(e, "copying maps");
     return SDFDDGI_OK;
