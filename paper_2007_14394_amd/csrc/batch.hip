@@ -26,7 +26,7 @@ namespace sdfddgi {
 
 // The fields of a lane's scene that every sample reads.
 struct LaneScene {
-    LevelLds lv;
+    LevelCells lv;
     float xlo0, xlo1, xlo2, xhi0, xhi1, xhi2;
     float eps, t_max, relax;
     int max_steps;
@@ -45,22 +45,29 @@ __device__ __forceinline__ LaneScene lane_scene(const BatchScene &s) {
 // kernels with one level: a point inside the grid box is level 0, else the ray
 // escapes).
 template <bool kPrimary>
-__device__ __forceinline__ int batch_step(const LaneScene &d, float o0, float o1, float o2,
-                                          float w0, float w1, float w2, float &t, int &k,
-                                          float &x0, float &x1, float &x2, int &steps) {
-    if (t > d.t_max) { steps = k; return kMissTmax; }
-    x0 = fmaf(t, w0, o0); x1 = fmaf(t, w1, o1); x2 = fmaf(t, w2, o2);
-    const bool in = (x0 >= d.xlo0) & (x0 <= d.xhi0) & (x1 >= d.xlo1) & (x1 <= d.xhi1) &
-                    (x2 >= d.xlo2) & (x2 <= d.xhi2);
-    if (!in) { steps = k; return kMissExit; }
-    const float dist = trilinear<true>(d.lv, (x0 - d.lv.org0) * d.lv.inv,
-                                       (x1 - d.lv.org1) * d.lv.inv, (x2 - d.lv.org2) * d.lv.inv);
-    if (kPrimary && k == 0 && dist < 0.0f) { steps = 1; return kInside; }
-    if (dist < d.eps) { steps = k + 1; return kHit; }
-    t = fmaf(d.relax, dist, t);
+__device__ __forceinline__ int batch_step(const BatchArgs &a, const LaneScene &d, float o0, float o1,
+                                          float o2, float w0, float w1, float w2, float &t, int &k,
+                                          int &steps) {
+    const float x0 = fmaf(t, w0, o0), x1 = fmaf(t, w1, o1), x2 = fmaf(t, w2, o2);
+    const bool box = (x0 >= d.xlo0) & (x0 <= d.xhi0) & (x1 >= d.xlo1) & (x1 <= d.xhi1) &
+                     (x2 >= d.xlo2) & (x2 <= d.xhi2);
+    const bool over = t > d.t_max;
+    const bool in = box && !over;
+    float dist = 0.0f;
+    if (a.wide) {
+        if (in) dist = distance_inside<true, true>((GlobalBytes)a.cells, d.lv, x0, x1, x2);
+    } else {
+        if (in) dist = distance_inside<true, false>((GlobalBytes)a.cells, d.lv, x0, x1, x2);
+    }
+    const bool inside = kPrimary && k == 0 && dist < 0.0f;
+    const bool hit = dist < d.eps;
+    const bool last = k + 1 == d.max_steps;
+    int kind = inside ? kInside : hit ? kHit : last ? kHitExhausted : -1;
+    kind = over ? kMissTmax : !box ? kMissExit : kind;
+    steps = in ? k + 1 : k;
+    t = in && !inside && !hit ? fmaf(d.relax, dist, t) : t;
     ++k;
-    if (k == d.max_steps) { steps = k; return kHitExhausted; }
-    return -1;
+    return kind;
 }
 
 __device__ __forceinline__ void load_scenes(const BatchArgs &a, BatchScene *s_sc, int *s_base) {
@@ -113,8 +120,7 @@ __global__ __launch_bounds__(256) void batch_primary_kernel(BatchArgs a) {
     int staged = 0;
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     // blocks of the concatenated rays dealt to the XCDs in turn (see BlockFeeder)
-    BlockFeeder<kChunkSize, kBatchBlockRays / kChunkSize> feed;
-    feed.start();
+    BlockFeeder feed(kChunkSize, kBatchBlockRays / kChunkSize);
     bool active = false;
     int ray = 0, k = 0, sc = 0;
     float o0 = 0, o1 = 0, o2 = 0, w0 = 0, w1 = 0, w2 = 0, t = 0;
@@ -156,9 +162,8 @@ __global__ __launch_bounds__(256) void batch_primary_kernel(BatchArgs a) {
         int4 entry = make_int4(0, 0, 0, 0);
         if (active) {
             const float tt = t;
-            float x0, x1, x2;
             int steps = 0;
-            const int kind = batch_step<true>(d, o0, o1, o2, w0, w1, w2, t, k, x0, x1, x2, steps);
+            const int kind = batch_step<true>(a, d, o0, o1, o2, w0, w1, w2, t, k, steps);
             if (kind >= 0) {
                 if (kind == kHit || kind == kHitExhausted) {
                     hit_now = true;
@@ -197,9 +202,9 @@ __device__ __forceinline__ float3 batch_albedo(const BatchScene &s, float x0, fl
     if (!d.alb) return make_float3(s.alb0, s.alb1, s.alb2);
     int i0, i1, i2;
     float f0, f1, f2;
-    cell_of((x0 - d.org0) * d.inv, d.cmax0, i0, f0);
-    cell_of((x1 - d.org1) * d.inv, d.cmax1, i1, f1);
-    cell_of((x2 - d.org2) * d.inv, d.cmax2, i2, f2);
+    cell_of((x0 - d.org0) * d.inv, (float)d.cmax0, i0, f0);
+    cell_of((x1 - d.org1) * d.inv, (float)d.cmax1, i1, f1);
+    cell_of((x2 - d.org2) * d.inv, (float)d.cmax2, i2, f2);
     const uint32_t sy = d.arow, sz = d.aslice;
     const float *p = d.alb + 3u * ((uint32_t)i2 * sz + (uint32_t)i1 * sy + (uint32_t)i0);
     float out[3];
@@ -218,7 +223,7 @@ __device__ __forceinline__ float3 batch_albedo(const BatchScene &s, float x0, fl
 
 // Hit shading of every scene's queued hits (see hits_kernel).
 template <int kChunkSize>
-__global__ __launch_bounds__(256) void batch_hits_kernel(BatchArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void batch_hits_kernel(BatchArgs a) {
     __shared__ BatchScene s_sc[kMaxBatchScenes];
     __shared__ int s_base[kMaxBatchScenes];
     load_scenes(a, s_sc, s_base);
@@ -288,7 +293,8 @@ __global__ __launch_bounds__(256) void batch_hits_kernel(BatchArgs a) {
                         const float *lt = a.lights + 6 * sc;
                         l0 = lt[0]; l1 = lt[1]; l2 = lt[2];
                         hx0 = fmaf(ht, w0, po0); hx1 = fmaf(ht, w1, po1); hx2 = fmaf(ht, w2, po2);
-                        hit_normal<true>(s.lv, hx0, hx1, hx2, w0, w1, w2, n0, n1, n2);
+                        hit_normal<true, 1>((GlobalBytes)a.cells, s.lv, a.wide, hx0, hx1, hx2, w0, w1, w2, n0, n1,
+                                         n2);
                         const float ndl = fmaf(n2, l2, fmaf(n1, l1, n0 * l0));
                         if (ndl > 0.0f) {
                             o0 = fmaf(n0, s.bias, hx0);
@@ -310,9 +316,8 @@ __global__ __launch_bounds__(256) void batch_hits_kernel(BatchArgs a) {
             if (stepping == 0 && feed.exhausted) break;
         }
         if (mode == kBShadow) {
-            float x0, x1, x2;
             int steps = 0;
-            const int kind = batch_step<false>(d, o0, o1, o2, l0, l1, l2, t, k, x0, x1, x2, steps);
+            const int kind = batch_step<false>(a, d, o0, o1, o2, l0, l1, l2, t, k, steps);
             if (kind >= 0) {
                 vis = (kind == kHit || kind == kHitExhausted) ? 0 : 1;
                 k = steps;

@@ -16,8 +16,8 @@ constexpr int kPartStride = 32;  // ints between per-XCD work counters: one 128-
 // One cascade level as the kernels see it. org/inv/half are the binary32
 // roundings of origin, 1/spacing and spacing/2 (computed once in binary64).
 struct DevLevel {
-    const void *quad;   // [n2-1][n1-1][n0] corner quads (see trilinear in kernels.hip):
-                        // float4, or 4 x binary16 in the precision form
+    uint32_t line0, nb0, nb1;  // the level's cell bricks (see load_corners in
+                               // trace_common.h): first line, bricks along x and y
     const float *alb;   // [n2][n1][n0][3] or nullptr
     int n0, n1, n2;
     float org0, org1, org2;
@@ -29,15 +29,20 @@ struct DevLevel {
     float xlo0, xlo1, xlo2, xhi0, xhi1, xhi2;
 };
 
-// A cascade level as the trace loops read it, copied to LDS once per block. The
-// binary32 constants were computed once in binary64 on the host.
-struct LevelLds {
-    const void *quad;              // corner quads [n2-1][n1-1][n0], float4 or half4
-    const float *alb;              // albedo [n2][n1][n0][3] or nullptr
+// What every sample reads of its level: three 16-byte LDS reads. The binary32 constants
+// were computed once in binary64 on the host.
+struct __attribute__((aligned(16))) LevelCells {
     float org0, org1, org2, inv;   // (float)origin, (float)(1/spacing)
-    float cmax0, cmax1, cmax2;     // (float)(n-2): last cell index per axis
+    uint32_t cmax0, cmax1, cmax2;  // n-2: last cell index per axis
+    uint32_t line0;                // first line of the level's cell bricks
+    uint32_t nb0, nb1;             // bricks along x and y
     float half;                    // (float)(spacing/2)
-    uint32_t row, slice;           // quad strides: n0, n0*(n1-1)
+    uint32_t pad;
+};
+
+// A cascade level as the trace loops read it, copied to LDS once per block.
+struct LevelLds : LevelCells {
+    const float *alb;              // albedo [n2][n1][n0][3] or nullptr
     uint32_t arow, aslice;         // albedo strides: n0, n0*n1
 };
 
@@ -63,7 +68,11 @@ struct AnalyticArgs {
 struct TraceArgs {
     DevLevel lv[kMaxLevels];
     int nl;
-    int half_sdf;               // 1: the quads hold binary16 values
+    int half_sdf;               // 1: the bricks hold binary16 values
+    const char *cells;          // cell bricks of every level, 128-byte lines
+    int wide;                   // 1: a level's brick indices need 32-bit products
+    int nested;                 // levels 0 .. nested-1: each one's box within the next coarser's
+    uint32_t r_magic;           // floor(2^32 / R) + 1
     int P, R;
     int max_steps;
     int irr_res;
@@ -168,7 +177,15 @@ hipError_t launch_hits(const TraceArgs &a, const TraceGrid &grid, hipStream_t st
 hipError_t launch_shade(const TraceArgs &a, hipStream_t stream);
 hipError_t launch_blend(const BlendArgs &a, hipStream_t stream);
 hipError_t launch_sample(const SampleArgs &a, hipStream_t stream);
-hipError_t launch_pack_quads(const float *grid, int n0, int n1, int n2, bool half, void *quad,
+// Cell bricks of an n0 x n1 x n2 grid (see load_corners in trace_common.h).
+constexpr int kLineBytes = 128;
+struct CellShape {
+    uint32_t nb0, nb1, nb2;     // bricks per axis
+    __host__ __device__ int64_t lines() const { return (int64_t)nb0 * nb1 * nb2; }
+    bool wide;                  // 24-bit products do not cover its indices
+};
+CellShape cell_shape(int n0, int n1, int n2, bool half);
+hipError_t launch_pack_cells(const float *grid, int n0, int n1, int n2, bool half, char *cells,
                              hipStream_t stream);
 hipError_t launch_fill_u8(uint8_t *dst, uint8_t value, int64_t n, hipStream_t stream);
 // n0 floats s0 -> d0 and n1 floats s1 -> d1 (either count may be 0, its pointers then unused).
@@ -323,7 +340,7 @@ constexpr int kBatchCounters = kPartStride + kXcds * kPartStride;
 constexpr int kBatchBlockRays = 65536;  // rays per block of the XCD interleave
 
 struct BatchScene {
-    LevelLds lv;                          // its grid level (binary16 quads)
+    LevelLds lv;                          // its grid level (binary16 bricks)
     float xlo0, xlo1, xlo2, xhi0, xhi1, xhi2;   // exact x bounds of the grid box
     ProbeGridDev pg;
     int P, R, ray_base, probe_base, dir_base, max_steps;
@@ -336,6 +353,8 @@ struct BatchScene {
 
 struct BatchArgs {
     int nscenes;
+    const char *cells;                    // cell bricks of every scene's grid
+    int wide;                             // 1: brick indices need 32-bit products
     const BatchScene *scenes;             // [nscenes]
     const float *lights;                  // [nscenes][6]: unit direction to the light, radiance
     int total_rays;

@@ -32,11 +32,10 @@ __device__ __forceinline__ void load_levels(const TraceArgs &a, LevelLds *s_lv) 
     if (threadIdx.x < kMaxLevels && (int)threadIdx.x < a.nl) {
         const DevLevel &d = a.lv[threadIdx.x];
         LevelLds v;
-        v.quad = d.quad; v.alb = d.alb;
+        v.line0 = d.line0; v.nb0 = d.nb0; v.nb1 = d.nb1; v.alb = d.alb;
         v.org0 = d.org0; v.org1 = d.org1; v.org2 = d.org2; v.inv = d.inv;
-        v.cmax0 = (float)(d.n0 - 2); v.cmax1 = (float)(d.n1 - 2); v.cmax2 = (float)(d.n2 - 2);
+        v.cmax0 = d.n0 - 2; v.cmax1 = d.n1 - 2; v.cmax2 = d.n2 - 2;
         v.half = d.half;
-        v.row = (uint32_t)d.n0; v.slice = (uint32_t)d.n0 * (uint32_t)(d.n1 - 1);
         v.arow = (uint32_t)d.n0; v.aslice = (uint32_t)d.n0 * (uint32_t)d.n1;
         s_lv[threadIdx.x] = v;
     }
@@ -47,16 +46,18 @@ __device__ __forceinline__ void load_levels(const TraceArgs &a, LevelLds *s_lv) 
 // holds x; -1 outside the coarsest box. The test "grid coordinate within [lo, hi]"
 // is made on x itself against per-level bounds: u = (x - org) * inv is monotone in x,
 // so the host finds the exact binary32 thresholds once and the result is the same.
+// Nested levels (`nested`, the usual cascade): no lane of the wave in a level's box, none
+// in the finer ones'.
 __device__ __forceinline__ int select_level(const TraceArgs &a, float x0, float x1, float x2) {
     int L = -1;
 #pragma unroll
     for (int l = kMaxLevels - 1; l >= 0; --l) {
-        if (l < a.nl) {
-            const DevLevel &d = a.lv[l];
-            const bool in = (x0 >= d.xlo0) & (x0 <= d.xhi0) & (x1 >= d.xlo1) & (x1 <= d.xhi1) &
-                            (x2 >= d.xlo2) & (x2 <= d.xhi2);
-            L = in ? l : L;
-        }
+        const DevLevel &d = a.lv[l];   // absent levels hold no point (an empty box)
+        const bool in = (x0 >= d.xlo0) & (x0 <= d.xhi0) & (x1 >= d.xlo1) & (x1 <= d.xhi1) &
+                        (x2 >= d.xlo2) & (x2 <= d.xhi2);
+        const uint64_t any = __ballot(in);
+        L = in ? l : L;
+        if (l > 0 && l < kMaxLevels - 1 && !any && a.nested >= l) break;
     }
     return L;
 }
@@ -74,43 +75,80 @@ __device__ __forceinline__ void load_sdf(const TraceArgs &a, SdfLds<kSdf> &s) {
     else load_levels(a, s.lv);
 }
 
-// One sample of the fixed sphere-trace sequence for a ray o + t w at sample k.
-// Returns the outcome code when the ray stops here (steps in *steps), -1 otherwise
-// (t and k are then advanced). x and the level of the sample are returned too.
+// Kernel arguments that only rare branches of a trace loop need, read where they are
+// used: hoisted out of the loop like other uniform values they would take the scalar
+// registers that every sample's level bounds need. The struct is the kernel's only
+// argument, at the start of its argument segment.
+typedef const __attribute__((address_space(4))) TraceArgs RareArgs;
+__device__ __forceinline__ RareArgs *rare_args() {
+    RareArgs *p = (RareArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Whether the calling lane is in a wave-uniform mask.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// The bricks' address, kept in scalar registers through a trace loop.
+__device__ __forceinline__ GlobalBytes kept_cells(const TraceArgs &a) {
+    GlobalBytes p = (GlobalBytes)a.cells;
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// One sample of the fixed sphere-trace sequence, at sample k of rays o + t w, for the
+// lanes of `live`; returns those whose ray goes on. There t and k are advanced; where a
+// ray stops they stay, and stop_kind names the outcome from them, the sample's distance
+// and its level (-1 outside every level). Other lanes' values stay as they are.
 // Analytic backend: no grid box, so a ray misses only past t_max; the distance is
 // the culled minimum over the primitives, starting from `bound` (the previous
 // sample's bound, +inf at a ray's first sample), and a primary ray's sample names
 // its nearest primitive in `slot` (level is 0).
-template <bool kPrimary, int kSdf>
-__device__ __forceinline__ int trace_step(const TraceArgs &a, const SdfLds<kSdf> &s, float o0,
-                                          float o1, float o2, float w0, float w1, float w2,
-                                          float &t, int &k, float &x0, float &x1, float &x2,
-                                          int &level, int &steps, float &bound, int &slot) {
-    if (t > a.t_max) { steps = k; return kMissTmax; }
-    x0 = fmaf(t, w0, o0); x1 = fmaf(t, w1, o1); x2 = fmaf(t, w2, o2);
-    float dist;
+template <bool kPrimary, int kSdf, bool kWide>
+__device__ __forceinline__ uint64_t trace_step(const TraceArgs &a, GlobalBytes cells,
+                                               const SdfLds<kSdf> &s, uint64_t live, float o0,
+                                               float o1, float o2, float w0, float w1, float w2,
+                                               float &t, int &k, float &dist, int &level,
+                                               float &bound, int &slot) {
+    const float x0 = fmaf(t, w0, o0), x1 = fmaf(t, w1, o1), x2 = fmaf(t, w2, o2);
+    uint64_t inside = live & ~__ballot(t > a.t_max);
     if constexpr (kSdf == kSdfAnalytic) {
         level = 0;
-        if (kPrimary) {
-            dist = nearest_distance(a.an, s.cl, x0, x1, x2, bound, slot);
-        } else {
-            uint32_t evals = 0;
-            dist = scene_distance(a.an, s.cl, 2, x0, x1, x2, bound, evals);
+        if (in_mask(inside)) {
+            if (kPrimary) {
+                dist = nearest_distance(a.an, s.cl, x0, x1, x2, bound, slot);
+            } else {
+                uint32_t evals = 0;
+                dist = scene_distance(a.an, s.cl, 2, x0, x1, x2, bound, evals);
+            }
         }
     } else {
-        level = select_level(a, x0, x1, x2);
-        if (level < 0) { steps = k; return kMissExit; }
-        const LevelLds &d = s.lv[level];
-        dist = trilinear<kSdf == kSdfGrid16>(d, (x0 - d.org0) * d.inv, (x1 - d.org1) * d.inv,
-                                             (x2 - d.org2) * d.inv);
+        constexpr bool kHalf = kSdf == kSdfGrid16;
+        const int found = select_level(a, x0, x1, x2);
+        inside &= __ballot(found >= 0);
+        level = in_mask(live) ? found : level;
+        if (in_mask(inside))
+            dist = distance_inside<kHalf, kWide>(cells, s.lv[found], x0, x1, x2);
     }
-    if (kPrimary && k == 0 && dist < 0.0f) { steps = 1; return kInside; }
-    if (dist < a.eps) { steps = k + 1; return kHit; }
-    t = fmaf(a.relax, dist, t);
-    if constexpr (kSdf == kSdfAnalytic) bound = next_bound(a.relax, dist);
-    ++k;
-    if (k == a.max_steps) { steps = k; return kHitExhausted; }
-    return -1;
+    const uint64_t go = inside & ~__ballot(dist < a.eps) & ~__ballot(k + 1 == a.max_steps);
+    if (in_mask(go)) {
+        t = fmaf(a.relax, dist, t);
+        ++k;
+        if (kSdf == kSdfAnalytic) bound = next_bound(a.relax, dist);
+    }
+    return go;
+}
+
+// The outcome of a ray that stopped, and its number of samples.
+template <bool kPrimary>
+__device__ __forceinline__ int stop_kind(const TraceArgs &a, float t, int k, float dist, int level,
+                                         int &steps) {
+    const bool over = t > a.t_max;
+    steps = over || level < 0 ? k : k + 1;
+    if (over) return kMissTmax;
+    if (level < 0) return kMissExit;
+    if (kPrimary && k == 0 && dist < 0.0f) return kInside;
+    return dist < a.eps ? kHit : kHitExhausted;
 }
 
 // ----------------------------------------------------------- radiometry -----
@@ -120,9 +158,9 @@ __device__ __forceinline__ float3 albedo_at(const TraceArgs &a, const LevelLds &
     if (!d.alb) return make_float3(a.alb0, a.alb1, a.alb2);
     int i0, i1, i2;
     float f0, f1, f2;
-    cell_of((x0 - d.org0) * d.inv, d.cmax0, i0, f0);
-    cell_of((x1 - d.org1) * d.inv, d.cmax1, i1, f1);
-    cell_of((x2 - d.org2) * d.inv, d.cmax2, i2, f2);
+    cell_of((x0 - d.org0) * d.inv, (float)d.cmax0, i0, f0);
+    cell_of((x1 - d.org1) * d.inv, (float)d.cmax1, i1, f1);
+    cell_of((x2 - d.org2) * d.inv, (float)d.cmax2, i2, f2);
     const uint32_t sy = d.arow, sz = d.aslice;
     const float *p = d.alb + 3u * ((uint32_t)i2 * sz + (uint32_t)i1 * sy + (uint32_t)i0);
     float out[3];
@@ -141,7 +179,8 @@ __device__ __forceinline__ float3 albedo_at(const TraceArgs &a, const LevelLds &
 
 // ------------------------------------------------------------- kernels ------
 
-__device__ __forceinline__ void write_record(const TraceArgs &a, int ray, float t, int kind,
+template <typename Args>
+__device__ __forceinline__ void write_record(const Args &a, int ray, float t, int kind,
                                              int level, int steps, int vis, int shadow_steps,
                                              float n0, float n1, float n2) {
     if (a.records) {
@@ -152,7 +191,8 @@ __device__ __forceinline__ void write_record(const TraceArgs &a, int ray, float 
     }
 }
 
-__device__ __forceinline__ void write_ray(const TraceArgs &a, int ray, float4 out, int kind,
+template <typename Args>
+__device__ __forceinline__ void write_ray(const Args &a, int ray, float4 out, int kind,
                                           int level, int steps, int vis, int shadow_steps,
                                           float n0, float n1, float n2) {
     a.payload[ray] = out;
@@ -173,8 +213,9 @@ __device__ __forceinline__ float4 shade_hit(const TraceArgs &a, float3 alb, floa
 
 // Per-wave staging of hit-queue entries (ray, bits of t, packed info, 0) in LDS;
 // flushed to the global queue 64 at a time with one atomic.
-__device__ __forceinline__ void flush_hits(const TraceArgs &a, int4 *buf, int count) {
+__device__ __forceinline__ void flush_hits(int4 *buf, int count) {
     if (count == 0) return;
+    RareArgs &a = *rare_args();
     int base = 0;
     if (__lane_id() == 0) base = atomicAdd(a.counter + 2, count);
     base = __builtin_amdgcn_readfirstlane(base);
@@ -183,139 +224,201 @@ __device__ __forceinline__ void flush_hits(const TraceArgs &a, int4 *buf, int co
     __builtin_amdgcn_wave_barrier();
 }
 
-constexpr int kChunk = 256;       // primary rays claimed from the global counter at a time
+constexpr int kChunk = 256;       // primary rays claimed from a counter at a time
+constexpr int kChunkSpread = 256; // ... while every wave of the grid gets this many
 constexpr int kHitChunk = 64;     // queued hits claimed at a time (spreads them over all waves)
-// Chunks per block of the XCD interleave (BlockFeeder): blocks of 256 probes keep
+// Rays per block of the XCD interleave (BlockFeeder): blocks of 65536 rays keep
 // the 8 XCDs on neighbouring blocks of the Morton order (one compact window for the
 // shared Infinity Cache and HBM) with a compact region per L2. Measured at 16384 x 256
 // (frame time, FP32 / FP16): one shared counter 0.862 / 0.758 ms; blocks of 1, 16,
-// 64, 256, 512 chunks 0.844, 0.833, 0.823, 0.799, 0.802 / -, -, 0.669, 0.652, 0.666;
+// 64, 256, 512 probes 0.844, 0.833, 0.823, 0.799, 0.802 / -, -, 0.669, 0.652, 0.666;
 // one contiguous part per XCD (blocks of 2048) was 1.6x slower than one counter.
-constexpr int kXcdBlock = 256;
+constexpr int kXcdBlockRays = 65536;
 constexpr int kRefillBelow = 32;  // refill / run batched work when fewer lanes are stepping
+constexpr int kEndBatch = 16;     // idle lanes at which a wave records ended rays and goes on
+constexpr int kFetchAt = 48;      // a wave fetches 64 more rays when no more than these wait
 constexpr int kAnalyticBin = 64;  // probes whose rays of one direction the analytic trace groups
 
-// Primary sphere trace, persistent and wave-compacted: each lane owns one ray and
-// takes one sample per iteration; when fewer than kRefillBelow lanes are stepping,
-// idle lanes take the next rays (kChunk per atomic: the rays of one probe, probes
-// visited in Morton order of their grid cell, blocks of that order dealt to the XCDs
-// in turn -- see BlockFeeder). Misses and probes inside geometry write their payload here; hits are
-// appended to a compact queue (ray, t, outcome, level, steps) for hits_kernel, staged
-// per wave in LDS. Each ray's arithmetic is the fixed sequence of trace_step,
-// whatever lane or wave runs it. Every wave exits once the counter has passed the
-// last ray and its lanes are idle, after flushing its staged hits.
-template <int kSdf>
+// Rays waiting to be traced by a wave, in LDS: origin and the distance stepped by the
+// first sample (0: not taken), direction and index.
+struct WaitingRay { float4 from, dir; };
+
+// Primary sphere trace, persistent and wave-compacted: each lane owns one ray and takes
+// one sample per iteration. Once kEndBatch lanes are idle the wave records the rays that
+// ended and gives those lanes the next rays of its queue, which it fills 64 at a time
+// ahead of need: runs of consecutive slots per atomic (rays of one probe, probes visited
+// in Morton order of their grid cell, blocks of that order dealt to the XCDs in turn --
+// see BlockFeeder), fetched in stages, one per iteration (the probe's index and the
+// direction; its position and first sample; into the queue), whose loads return beside
+// the iterations' own samples. Misses and probes inside geometry write their payload
+// here; hits are appended to a compact queue (ray, t, outcome, level, steps) for
+// hits_kernel, staged per wave in LDS. Each ray's arithmetic is the fixed sequence of
+// trace_step, whatever lane or wave runs it. Every wave exits once the counters have
+// passed the last ray and its lanes are idle, after flushing its staged hits.
+// Alone at 16384 x 256 (open scene): 431 us in binary32 and 353 us in binary16, 99 M and
+// 116 M vector instructions at 80 % of the lanes; taking rays straight into idle lanes
+// once half of a wave's had stopped, over corner quads: 530 and 467 us, 159 M and 168 M
+// at 57 %. More or fewer resident waves, direction-major ray orders over 64 to 16384
+// probes (each direction's rays side by side) and a lane-by-lane look-ahead in registers
+// (478 / 419 us) were no faster.
+template <int kSdf, bool kWide = false>
 __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
     __shared__ SdfLds<kSdf> s_sdf;
     __shared__ int4 s_hits[4][64];
+    // the primitives' LDS leaves room for the fetch in hand only
+    constexpr int kRayQueue = kSdf == kSdfAnalytic ? 64 : 128;
+    constexpr int kQueueAhead = kSdf == kSdfAnalytic ? 0 : kFetchAt;
+    __shared__ WaitingRay s_rays[4][kRayQueue];
     load_sdf<kSdf>(a, s_sdf);
+    const GlobalBytes cells = kept_cells(a);
     const int lane = (int)__lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int staged = 0;  // wave-uniform count of entries in s_hits[wave]
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const int total = (a.probe_count ? *a.probe_count : a.P) * a.R;
-    BlockFeeder<kChunk, kXcdBlock> feed;
-    feed.start();
-    bool active = false;
-    int ray = 0, k = 0, slot = -1;
-    float o0 = 0, o1 = 0, o2 = 0, w0 = 0, w1 = 0, w2 = 0, t = 0, bound = INFINITY;
+    const int total =
+        __builtin_amdgcn_readfirstlane((a.probe_count ? *a.probe_count : a.P) * a.R);
+    // whole probes per claim, and rays queued ahead, while that still gives every wave
+    // several; else few rays spread over all waves. Likewise the XCDs' blocks
+    const bool plenty = total / kChunkSpread >= (int)gridDim.x * 4;
+    const int chunk = plenty ? kChunk : 64;
+    BlockFeeder feed(chunk, max(1, min(kXcdBlockRays, total / (4 * kXcds)) / chunk));
+    // lanes that are stepping; that stopped and are not recorded
+    uint64_t live = 0, ended = 0;
+    int staged = 0;                 // hits in s_hits[wave]
+    int head = 0, waiting = 0;      // first and number of the rays in s_rays[wave]
+    int stage = 0, coming = 0;      // a fetch's stage (0: none), lanes 0 .. coming-1 have a ray
+    int ray = 0, k = 0, level = 0, slot = -1, n_ray = 0, n_probe = 0;
+    float o0 = 0, o1 = 0, o2 = 0, w0 = 0, w1 = 0, w2 = 0, t = 0, dist = 0, bound = INFINITY;
+    float m0 = 0, m1 = 0, m2 = 0, v0 = 0, v1 = 0, v2 = 0;
+    int2 n_first = make_int2(0, -1);
     while (true) {
-        uint64_t stepping = __ballot(active);
-        if (__popcll(stepping) < kRefillBelow) {
-            uint64_t idle = ~stepping;
-            while (idle != 0 && !feed.exhausted) {
-                int first = 0;
-                const int n = feed.claim(a.parts, total, __popcll(idle), first);
-                const int rank = __popcll(idle & below);
-                if (!active && rank < n) {
-                    // slot -> (probe in Morton order, ray): neighbouring slots trace
-                    // neighbouring probes, so the rays in flight share cache lines
-                    const int sid = first + rank;
-                    int q, i;
-                    if constexpr (kSdf == kSdfAnalytic) {
-                        // groups of kAnalyticBin probes of the Morton order, consecutive
-                        // slots taking one direction across the group's probes: a wave's
-                        // lanes march side by side from neighbouring probes, so the
-                        // clusters that any lane's bound admits stay few
-                        const int nq = total / a.R, gsz = kAnalyticBin * a.R;
-                        const int g = sid / gsz, within = sid - g * gsz;
-                        const int gq = min(kAnalyticBin, nq - g * kAnalyticBin);
-                        i = within / gq;
-                        q = g * kAnalyticBin + (within - i * gq);
-                    } else {
-                        q = sid / a.R;
-                        i = sid - q * a.R;
-                    }
-                    const int p = a.probe_order[q];
-                    ray = p * a.R + i;
-                    o0 = a.probe_pos[3 * p]; o1 = a.probe_pos[3 * p + 1]; o2 = a.probe_pos[3 * p + 2];
-                    w0 = a.dirs[3 * i]; w1 = a.dirs[3 * i + 1]; w2 = a.dirs[3 * i + 2];
-                    t = 0.0f;
-                    k = 0;
-                    bound = INFINITY;
-                    if (a.probe_first && a.max_steps > 1) {
-                        // the first sample sits at the probe (fma(0, w, o) = o) for every
-                        // ray of it: where that sample only steps on (a level holds the
-                        // probe, or the primitives are traced; distance >= eps), take
-                        // the step from the probe's precomputed sample; otherwise the
-                        // first trace_step samples
-                        const int2 f = a.probe_first[p];
-                        const float d0 = __int_as_float(f.x);
-                        if ((kSdf == kSdfAnalytic || f.y >= 0) && !(d0 < a.eps)) {
-                            t = fmaf(a.relax, d0, 0.0f);
-                            k = 1;
-                            if constexpr (kSdf == kSdfAnalytic) {
-                                bound = next_bound(a.relax, d0);
-                                slot = f.y;
-                            }
-                        }
-                    }
-                    active = true;
-                }
-                idle = __ballot(!active);
+        if (stage == 2) {
+            RareArgs &f = *rare_args();
+            if (lane < coming) {
+                // the first sample sits at the probe (fma(0, w, o) = o) for every
+                // ray of it: where that sample only steps on (a level holds the
+                // probe, or the primitives are traced; distance >= eps), take
+                // the step from the probe's precomputed sample; otherwise the
+                // first trace_step samples
+                const float d0 = __int_as_float(n_first.x);
+                const bool known = f.probe_first && a.max_steps > 1 &&
+                                   (kSdf == kSdfAnalytic || n_first.y >= 0) && !(d0 < a.eps);
+                WaitingRay &r = s_rays[wave][(head + waiting + lane) & (kRayQueue - 1)];
+                r.from = make_float4(m0, m1, m2, known ? d0 : 0.0f);
+                r.dir = make_float4(v0, v1, v2, __int_as_float(n_probe * f.R + n_ray));
             }
-            stepping = __ballot(active);
-            if (stepping == 0) {  // counter exhausted and every lane idle
-                flush_hits(a, s_hits[wave], staged);
-                break;
-            }
-        }
-        bool hit_now = false;
-        int4 entry = make_int4(0, 0, 0, 0);
-        if (active) {
-            const float tt = t;
-            float x0, x1, x2;
-            int level = 0, steps = 0;
-            const int kind = trace_step<true, kSdf>(a, s_sdf, o0, o1, o2, w0, w1, w2, t, k, x0,
-                                                    x1, x2, level, steps, bound, slot);
-            if (kind >= 0) {
-                if (kind == kHit || kind == kHitExhausted) {
-                    hit_now = true;
-                    entry = make_int4(ray, __float_as_int(tt), pack_hit(kind, level, steps),
-                                      kSdf == kSdfAnalytic ? slot : 0);
-                } else {
-                    const float4 out = kind == kInside ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
-                                                       : make_float4(a.sky0, a.sky1, a.sky2, a.t_max);
-                    write_ray(a, ray, out, kind, 0, steps, -1, 0, 0.0f, 0.0f, 0.0f);
-                }
-                active = false;
-            }
-        }
-        const uint64_t hm = __ballot(hit_now);
-        if (hm) {
-            const int n = __popcll(hm);
-            if (staged + n > 64) {
-                flush_hits(a, s_hits[wave], staged);
-                staged = 0;
-            }
-            if (hit_now) s_hits[wave][staged + __popcll(hm & below)] = entry;
             __builtin_amdgcn_wave_barrier();
-            staged += n;
-            if (staged == 64) {
-                flush_hits(a, s_hits[wave], staged);
-                staged = 0;
+            waiting += coming;
+            stage = 0;
+        } else if (stage == 1) {
+            RareArgs &f = *rare_args();
+            if (lane < coming) {
+                m0 = f.probe_pos[3 * n_probe];
+                m1 = f.probe_pos[3 * n_probe + 1];
+                m2 = f.probe_pos[3 * n_probe + 2];
+                if (f.probe_first) n_first = f.probe_first[n_probe];
+            }
+            stage = 2;
+        }
+        if (__popcll(live) <= 64 - kEndBatch) {
+            if (ended) {
+                RareArgs &f = *rare_args();
+                bool hit = false;
+                int4 entry = make_int4(0, 0, 0, 0);
+                if (in_mask(ended)) {
+                    int steps;
+                    const int kind = stop_kind<true>(a, t, k, dist, level, steps);
+                    if (kind == kHit || kind == kHitExhausted) {
+                        hit = true;
+                        entry = make_int4(ray, __float_as_int(t), pack_hit(kind, level, steps),
+                                          kSdf == kSdfAnalytic ? slot : 0);
+                    } else {
+                        const float4 out = kind == kInside
+                                               ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
+                                               : make_float4(f.sky0, f.sky1, f.sky2, a.t_max);
+                        write_ray(f, ray, out, kind, 0, steps, -1, 0, 0.0f, 0.0f, 0.0f);
+                    }
+                }
+                ended = 0;
+                const uint64_t hm = __ballot(hit);
+                if (hm) {
+                    const int n = __popcll(hm);
+                    if (staged + n > 64) {
+                        flush_hits(s_hits[wave], staged);
+                        staged = 0;
+                    }
+                    if (hit) s_hits[wave][staged + __popcll(hm & below)] = entry;
+                    __builtin_amdgcn_wave_barrier();
+                    staged += n;
+                }
+            }
+            if (waiting > 0) {
+                const int rank = __popcll(~live & below);
+                const uint64_t take = __ballot(in_mask(~live) && rank < waiting);
+                if (in_mask(take)) {
+                    const WaitingRay r = s_rays[wave][(head + rank) & (kRayQueue - 1)];
+                    o0 = r.from.x; o1 = r.from.y; o2 = r.from.z;
+                    w0 = r.dir.x; w1 = r.dir.y; w2 = r.dir.z;
+                    ray = __float_as_int(r.dir.w);
+                    const float d0 = r.from.w;
+                    t = fmaf(a.relax, d0, 0.0f);
+                    k = d0 != 0.0f ? 1 : 0;
+                    if constexpr (kSdf == kSdfAnalytic)
+                        bound = d0 != 0.0f ? next_bound(a.relax, d0) : INFINITY;
+                }
+                __builtin_amdgcn_wave_barrier();
+                live |= take;
+                const int n = __popcll(take);
+                head += n;
+                waiting -= n;
+            }
+            if (stage == 0 && !feed.exhausted &&
+                (plenty ? waiting <= kQueueAhead : __popcll(live) <= 32)) {
+                RareArgs &f = *rare_args();
+                coming = 0;
+                while (coming < 64 && !feed.exhausted) {
+                    int first = 0;
+                    const int n = feed.claim(f.parts, total, 64 - coming, first);
+                    if (lane >= coming && lane < coming + n) {
+                        // slot -> (probe in Morton order, ray): neighbouring slots trace
+                        // neighbouring probes, so the rays in flight share cache lines
+                        const int sid = first + lane - coming;
+                        int q, i;
+                        if constexpr (kSdf == kSdfAnalytic) {
+                            // groups of kAnalyticBin probes of the Morton order, consecutive
+                            // slots taking one direction across the group's probes: a wave's
+                            // lanes march side by side from neighbouring probes, so the
+                            // clusters that any lane's bound admits stay few
+                            const int nq = total / f.R, gsz = kAnalyticBin * f.R;
+                            const int g = sid / gsz, within = sid - g * gsz;
+                            const int gq = min(kAnalyticBin, nq - g * kAnalyticBin);
+                            i = within / gq;
+                            q = g * kAnalyticBin + (within - i * gq);
+                        } else {
+                            // sid / R: at most one too large (sid < 2^31, R <= 2^10)
+                            q = (int)__umulhi((uint32_t)sid, f.r_magic);
+                            i = sid - q * f.R;
+                            if (i < 0) { --q; i += f.R; }
+                        }
+                        n_probe = f.probe_order[q];
+                        v0 = f.dirs[3 * i]; v1 = f.dirs[3 * i + 1]; v2 = f.dirs[3 * i + 2];
+                        n_ray = i;
+                    }
+                    coming += n;
+                }
+                stage = coming ? 1 : 0;
+            }
+            if (!live) {  // then no ray waits either
+                if (stage == 0 && feed.exhausted) {
+                    flush_hits(s_hits[wave], staged);
+                    break;
+                }
+                continue;
             }
         }
+        const uint64_t go = trace_step<true, kSdf, kWide>(a, cells, s_sdf, live, o0, o1, o2, w0, w1, w2,
+                                                   t, k, dist, level, bound, slot);
+        ended |= live & ~go;
+        live = go;
     }
 }
 
@@ -327,10 +430,11 @@ constexpr int kShadeBatch = 16;   // shade when this many lanes wait (or steppin
 // newly assigned lanes), the SDF shadow ray toward the light (wave-compacted like the
 // primary trace), and shading -- albedo, sun, multi-bounce lookup -- batched when
 // kShadeBatch lanes wait or stepping runs low.
-template <int kSdf>
-__global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
+template <int kSdf, bool kWide = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hits_kernel(TraceArgs a) {
     __shared__ SdfLds<kSdf> s_sdf;
     load_sdf<kSdf>(a, s_sdf);
+    const GlobalBytes cells = kept_cells(a);
     const int lane = (int)__lane_id();
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const int total = a.counter[2];  // queue length, final once primary_kernel has finished
@@ -338,7 +442,8 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
 
     int mode = kIdle, ray = 0, info = 0, k = 0, vis = -1, slot = 0, qi = 0;
     float ht = 0, hx0 = 0, hx1 = 0, hx2 = 0, n0 = 0, n1 = 0, n2 = 0;
-    float o0 = 0, o1 = 0, o2 = 0, t = 0, bound = INFINITY;
+    float o0 = 0, o1 = 0, o2 = 0, t = 0, dist = 0, bound = INFINITY;
+    int level = 0;
     while (true) {
         uint64_t stepping = __ballot(mode == kShadow);
         const int waiting = __popcll(__ballot(mode == kPendShade));
@@ -401,8 +506,9 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
                         if constexpr (kSdf == kSdfAnalytic)
                             analytic_normal(s_sdf.cl, slot, hx0, hx1, hx2, w0, w1, w2, n0, n1, n2);
                         else
-                            hit_normal<kSdf == kSdfGrid16>(s_sdf.lv[(info >> 4) & 15], hx0, hx1,
-                                                           hx2, w0, w1, w2, n0, n1, n2);
+                            hit_normal<kSdf == kSdfGrid16>(cells, s_sdf.lv[(info >> 4) & 15],
+                                                           kWide, hx0, hx1, hx2, w0, w1, w2, n0,
+                                                           n1, n2);
                         const float ndl = fmaf(n2, a.l2, fmaf(n1, a.l1, n0 * a.l0));
                         if (ndl > 0.0f) {
                             o0 = fmaf(n0, a.bias, hx0);
@@ -423,17 +529,16 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
             stepping = __ballot(mode == kShadow);
             if (stepping == 0 && feed.exhausted) break;
         }
-        if (mode == kShadow) {
-            float x0, x1, x2;
-            int level = 0, steps = 0;
-            int unused = 0;
-            const int kind = trace_step<false, kSdf>(a, s_sdf, o0, o1, o2, a.l0, a.l1, a.l2, t,
-                                                     k, x0, x1, x2, level, steps, bound, unused);
-            if (kind >= 0) {
-                vis = (kind == kHit || kind == kHitExhausted) ? 0 : 1;
-                k = steps;
-                mode = kPendShade;
-            }
+        const uint64_t live = __ballot(mode == kShadow);
+        int unused = 0;
+        const uint64_t go = trace_step<false, kSdf, kWide>(a, cells, s_sdf, live, o0, o1, o2, a.l0, a.l1,
+                                                    a.l2, t, k, dist, level, bound, unused);
+        if (in_mask(live & ~go)) {
+            int steps;
+            const int kind = stop_kind<false>(a, t, k, dist, level, steps);
+            vis = (kind == kHit || kind == kHitExhausted) ? 0 : 1;
+            k = steps;
+            mode = kPendShade;
         }
     }
 }
@@ -711,10 +816,10 @@ __global__ __launch_bounds__(256) void relocate_kernel(TraceArgs a, RelocateArgs
     for (int it = 0; it < r.iterations; ++it) {
         const int L = select_level(a, x0, x1, x2);
         if (L < 0) break;
-        const float d = sample_at<kHalf>(s_lv[L], x0, x1, x2);
+        const float d = sample_at<kHalf>((GlobalBytes)a.cells, s_lv[L], a.wide, x0, x1, x2);
         if (!(d < r.t1)) break;
         float n0, n1, n2;
-        hit_normal<kHalf>(s_lv[L], x0, x1, x2, 0.0f, -1.0f, 0.0f, n0, n1, n2);
+        hit_normal<kHalf>((GlobalBytes)a.cells, s_lv[L], a.wide, x0, x1, x2, 0.0f, -1.0f, 0.0f, n0, n1, n2);
         const float step = r.t1 - d;
         x0 = fminf(fmaxf(fmaf(step, n0, x0), lo0), hi0);
         x1 = fminf(fmaxf(fmaf(step, n1, x1), lo1), hi1);
@@ -737,7 +842,7 @@ __global__ __launch_bounds__(256) void probe_sdf_kernel(TraceArgs a, float *out)
     if (p >= a.P) return;
     const float x0 = a.probe_pos[3 * p], x1 = a.probe_pos[3 * p + 1], x2 = a.probe_pos[3 * p + 2];
     const int L = select_level(a, x0, x1, x2);
-    out[p] = L < 0 ? 1e30f : sample_at<kHalf>(s_lv[L], x0, x1, x2);
+    out[p] = L < 0 ? 1e30f : sample_at<kHalf>((GlobalBytes)a.cells, s_lv[L], a.wide, x0, x1, x2);
 }
 
 // Each probe's first sample: the level its position selects and the distance there,
@@ -750,7 +855,7 @@ __global__ __launch_bounds__(256) void probe_first_kernel(TraceArgs a, int2 *out
     if (p >= a.P) return;
     const float x0 = a.probe_pos[3 * p], x1 = a.probe_pos[3 * p + 1], x2 = a.probe_pos[3 * p + 2];
     const int L = select_level(a, x0, x1, x2);
-    const float d = L < 0 ? 0.0f : sample_at<kHalf>(s_lv[L], x0, x1, x2);
+    const float d = L < 0 ? 0.0f : sample_at<kHalf>((GlobalBytes)a.cells, s_lv[L], a.wide, x0, x1, x2);
     out[p] = make_int2(__float_as_int(d), L);
 }
 
@@ -778,39 +883,39 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs a) {
     a.out[3 * q + 2] = e.z;
 }
 
-// Corner-quad repacking of one grid level (see trilinear). The binary16 form clamps
-// each value to +-65504 and rounds it to nearest even.
+// Cell bricks of one grid level (see load_corners), one thread per vertex column of a
+// brick; past the grid's last vertex a column repeats it (no cell reads those). The
+// binary16 form clamps each value to +-65504 and rounds it to nearest even.
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ _Float16 to_half(float v) {
     return (_Float16)fminf(fmaxf(v, -65504.0f), 65504.0f);
 }
 
-__global__ __launch_bounds__(256) void pack_quads_half_kernel(const float *__restrict__ g, int n0,
-                                                              int n1, int n2,
-                                                              half4_t *__restrict__ quad) {
-    const int64_t total = (int64_t)n0 * (n1 - 1) * (n2 - 1);
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    const int i = (int)(q % n0);
-    const int j = (int)((q / n0) % (n1 - 1));
-    const int k = (int)(q / ((int64_t)n0 * (n1 - 1)));
-    const int64_t sy = n0, sz = (int64_t)n0 * n1;
-    const int64_t v = k * sz + j * sy + i;
-    half4_t h;
-    h.x = to_half(g[v]); h.y = to_half(g[v + sy]); h.z = to_half(g[v + sz]); h.w = to_half(g[v + sz + sy]);
-    quad[q] = h;
-}
-
-__global__ __launch_bounds__(256) void pack_quads_kernel(const float *__restrict__ g, int n0, int n1,
-                                                         int n2, float4 *__restrict__ quad) {
-    const int64_t total = (int64_t)n0 * (n1 - 1) * (n2 - 1);
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    const int i = (int)(q % n0);
-    const int j = (int)((q / n0) % (n1 - 1));
-    const int k = (int)(q / ((int64_t)n0 * (n1 - 1)));
-    const int64_t sy = n0, sz = (int64_t)n0 * n1;
-    const int64_t v = k * sz + j * sy + i;
-    quad[q] = make_float4(g[v], g[v + sy], g[v + sz], g[v + sz + sy]);
+template <bool kHalf>
+__global__ __launch_bounds__(256) void pack_cells_kernel(const float *__restrict__ g, int n0, int n1,
+                                                         int n2, CellShape sh,
+                                                         char *__restrict__ cells) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t line = e >> 4;
+    if (line >= sh.lines()) return;
+    const int col = (int)(e & 15);
+    const int64_t row = line / sh.nb0;
+    const int64_t b0 = line - row * sh.nb0, b2 = row / sh.nb1, b1 = row - b2 * sh.nb1;
+    const int64_t i = min(3 * b0 + (col & 3), (int64_t)n0 - 1);
+    const int64_t j = min(3 * b1 + (col >> 2), (int64_t)n1 - 1);
+    const auto at = [&](int64_t k) {
+        return g[(min(k, (int64_t)n2 - 1) * n1 + j) * n0 + i];
+    };
+    char *out = cells + line * kLineBytes + col * 8;
+    if (kHalf) {
+        half4_t h;
+        h.x = to_half(at(3 * b2)); h.y = to_half(at(3 * b2 + 1));
+        h.z = to_half(at(3 * b2 + 2)); h.w = to_half(at(3 * b2 + 3));
+        *reinterpret_cast<half4_t *>(out) = h;
+    } else {
+        *reinterpret_cast<float2 *>(out) = make_float2(at(b2), at(b2 + 1));
+    }
 }
 
 __global__ __launch_bounds__(256) void fill_u8_kernel(uint8_t *dst, uint8_t value, int64_t n) {
@@ -914,26 +1019,32 @@ TraceGrid trace_grid(int device, int64_t rays, bool half, bool analytic) {
     return g;
 }
 
+// The kernel of a context's distance backend.
+#define SDFDDGI_LAUNCH_TRACE(kernel, blocks)                                                       \
+    do {                                                                                           \
+        if (a.analytic)                                                                            \
+            hipLaunchKernelGGL(kernel<kSdfAnalytic>, dim3(blocks), dim3(256), 0, s, a);            \
+        else if (a.half_sdf && a.wide)                                                             \
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(kernel<kSdfGrid16, true>), dim3(blocks), dim3(256), \
+                               0, s, a);                                                           \
+        else if (a.half_sdf)                                                                       \
+            hipLaunchKernelGGL(kernel<kSdfGrid16>, dim3(blocks), dim3(256), 0, s, a);              \
+        else if (a.wide)                                                                           \
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(kernel<kSdfGrid32, true>), dim3(blocks), dim3(256), \
+                               0, s, a);                                                           \
+        else                                                                                       \
+            hipLaunchKernelGGL(kernel<kSdfGrid32>, dim3(blocks), dim3(256), 0, s, a);              \
+    } while (0)
+
 hipError_t launch_primary(const TraceArgs &a, const TraceGrid &g, hipStream_t s) {
     if ((int64_t)a.P * a.R == 0) return hipSuccess;
-    if (a.analytic)
-        hipLaunchKernelGGL(primary_kernel<kSdfAnalytic>, dim3(g.primary_blocks), dim3(256), 0, s,
-                           a);
-    else if (a.half_sdf)
-        hipLaunchKernelGGL(primary_kernel<kSdfGrid16>, dim3(g.primary_blocks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(primary_kernel<kSdfGrid32>, dim3(g.primary_blocks), dim3(256), 0, s, a);
+    SDFDDGI_LAUNCH_TRACE(primary_kernel, g.primary_blocks);
     return hipGetLastError();
 }
 
 hipError_t launch_hits(const TraceArgs &a, const TraceGrid &g, hipStream_t s) {
     if ((int64_t)a.P * a.R == 0) return hipSuccess;
-    if (a.analytic)
-        hipLaunchKernelGGL(hits_kernel<kSdfAnalytic>, dim3(g.hits_blocks), dim3(256), 0, s, a);
-    else if (a.half_sdf)
-        hipLaunchKernelGGL(hits_kernel<kSdfGrid16>, dim3(g.hits_blocks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(hits_kernel<kSdfGrid32>, dim3(g.hits_blocks), dim3(256), 0, s, a);
+    SDFDDGI_LAUNCH_TRACE(hits_kernel, g.hits_blocks);
     return hipGetLastError();
 }
 
@@ -997,15 +1108,25 @@ hipError_t launch_sample(const SampleArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_pack_quads(const float *g, int n0, int n1, int n2, bool half, void *quad,
+CellShape cell_shape(int n0, int n1, int n2, bool half) {
+    CellShape s{};
+    s.nb0 = (uint32_t)(n0 - 1 + 2) / 3;
+    s.nb1 = (uint32_t)(n1 - 1 + 2) / 3;
+    s.nb2 = half ? (uint32_t)(n2 - 1 + 2) / 3 : (uint32_t)(n2 - 1);
+    s.wide = n0 > 65536 || n1 > 65536 || n2 > 65536 || (int64_t)s.nb2 * s.nb1 >= (int64_t)1 << 24;
+    return s;
+}
+
+hipError_t launch_pack_cells(const float *g, int n0, int n1, int n2, bool half, char *cells,
                              hipStream_t s) {
-    const int64_t total = (int64_t)n0 * (n1 - 1) * (n2 - 1);
+    const CellShape sh = cell_shape(n0, n1, n2, half);
+    const unsigned blocks = blocks_for(sh.lines() * 16, 256);
     if (half)
-        hipLaunchKernelGGL(pack_quads_half_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, s, g,
-                           n0, n1, n2, static_cast<half4_t *>(quad));
+        hipLaunchKernelGGL(pack_cells_kernel<true>, dim3(blocks), dim3(256), 0, s, g, n0, n1, n2, sh,
+                           cells);
     else
-        hipLaunchKernelGGL(pack_quads_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, s, g, n0,
-                           n1, n2, static_cast<float4 *>(quad));
+        hipLaunchKernelGGL(pack_cells_kernel<false>, dim3(blocks), dim3(256), 0, s, g, n0, n1, n2,
+                           sh, cells);
     return hipGetLastError();
 }
 

@@ -145,8 +145,10 @@ struct sdfddgi_ctx {
     int n[kMaxLevels][3]{};
     double origin[kMaxLevels][3]{};
     double spacing[kMaxLevels]{};
-    void *quad[kMaxLevels]{};    // corner-quad repacking of each level's grid
-    bool half = false;           // precision form: quads in binary16
+    char *cells = nullptr;       // cell bricks of every level (see load_corners)
+    uint32_t line0[kMaxLevels]{};    // each level's first line there
+    bool wide = false;           // some level's brick indices need 32-bit products
+    bool half = false;           // precision form: bricks in binary16
     float *alb[kMaxLevels]{};
     sdfddgi_probe_grid pg{};
     int64_t P = 0;
@@ -306,9 +308,9 @@ void free_set(RaySet &r) {
 
 void free_all(sdfddgi_ctx *c) {
     for (int L = 0; L < kMaxLevels; ++L) {
-        dev_free(c->quad[L]);
         dev_free(c->alb[L]);
     }
+    dev_free(c->cells);
     free_set(c->main);
     free_set(c->spare);
     for (RaySet *r : {&c->low[0], &c->low[1], &c->fbs[0], &c->fbs[1]}) {
@@ -565,7 +567,10 @@ float upper_bound_x(float org, float inv, float hi) {
 
 DevLevel dev_level(const sdfddgi_ctx *c, int L) {
     DevLevel d{};
-    d.quad = c->quad[L];
+    const CellShape sh = cell_shape(c->n[L][0], c->n[L][1], c->n[L][2], c->half);
+    d.line0 = c->line0[L];
+    d.nb0 = sh.nb0;
+    d.nb1 = sh.nb1;
     d.alb = c->alb[L];
     d.n0 = c->n[L][0];
     d.n1 = c->n[L][1];
@@ -587,6 +592,12 @@ DevLevel dev_level(const sdfddgi_ctx *c, int L) {
     d.xlo0 = lo[0]; d.xlo1 = lo[1]; d.xlo2 = lo[2];
     d.xhi0 = hi[0]; d.xhi1 = hi[1]; d.xhi2 = hi[2];
     return d;
+}
+
+// Whether every point of fine's box is in coarse's.
+bool box_within(const DevLevel &fine, const DevLevel &coarse) {
+    return fine.xlo0 >= coarse.xlo0 && fine.xlo1 >= coarse.xlo1 && fine.xlo2 >= coarse.xlo2 &&
+           fine.xhi0 <= coarse.xhi0 && fine.xhi1 <= coarse.xhi1 && fine.xhi2 <= coarse.xhi2;
 }
 
 ProbeGridDev dev_probes(const sdfddgi_ctx *c) {
@@ -701,8 +712,12 @@ BlendArgs blend_args(const sdfddgi_ctx *c, const RaySet &r, const float4 *payloa
 TraceArgs trace_base(const sdfddgi_ctx *c, const float l[3], const float rad[3]) {
     TraceArgs t{};
     for (int L = 0; L < c->nl; ++L) t.lv[L] = dev_level(c, L);
+    for (int L = c->nl; L < kMaxLevels; ++L) t.lv[L].xlo0 = INFINITY;   // holds no point
+    while (t.nested + 1 < c->nl && box_within(t.lv[t.nested], t.lv[t.nested + 1])) ++t.nested;
     t.nl = c->nl;
     t.half_sdf = c->half ? 1 : 0;
+    t.cells = c->cells;
+    t.wide = c->wide ? 1 : 0;
     t.P = (int)c->P;
     t.max_steps = c->prm.max_steps;
     t.irr_res = c->prm.irr_res;
@@ -746,6 +761,7 @@ TraceArgs trace_pass(const TraceArgs &base, const RaySet &r, int *counters, int 
     TraceArgs t = base;
     t.parts = parts;
     t.R = r.R;
+    t.r_magic = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)r.R) + 1u;
     t.dirs = r.dirs;
     t.payload = r.payload;
     t.hitq = r.hitq;
@@ -897,6 +913,16 @@ static sdfddgi_status create_ctx(const sdfddgi_sdf_grid *sdf, const HostClusters
         if (e_ != hipSuccess) return bail(hip_fail(nullptr, e_, what));         \
     } while (0)
 
+    int64_t lines = 0;
+    for (int L = 0; L < c->nl; ++L) {
+        const sdfddgi_sdf_level &lv = sdf->level[L];
+        const CellShape sh = cell_shape(lv.n[0], lv.n[1], lv.n[2], c->half);
+        c->line0[L] = (uint32_t)lines;   // at most 4 x 2^28 lines
+        c->wide = c->wide || sh.wide;
+        lines += sh.lines();
+    }
+    c->wide = c->wide || lines * kLineBytes >= (int64_t)1 << 32;
+    SDF_TRY(dev_alloc(&c->cells, (size_t)lines * kLineBytes), "allocating the sdf levels");
     for (int L = 0; L < c->nl; ++L) {
         const sdfddgi_sdf_level &lv = sdf->level[L];
         const size_t cnt = (size_t)lv.n[0] * lv.n[1] * lv.n[2];
@@ -905,10 +931,8 @@ static sdfddgi_status create_ctx(const sdfddgi_sdf_grid *sdf, const HostClusters
             c->origin[L][k] = lv.origin[k];
         }
         c->spacing[L] = lv.spacing;
-        const size_t nquad = (size_t)lv.n[0] * (lv.n[1] - 1) * (lv.n[2] - 1);
-        SDF_TRY(hipMalloc(&c->quad[L], nquad * (c->half ? 8 : 16)), "allocating sdf level");
-        SDF_TRY(launch_pack_quads(lv.sdf, lv.n[0], lv.n[1], lv.n[2], c->half, c->quad[L],
-                                  c->stream),
+        SDF_TRY(launch_pack_cells(lv.sdf, lv.n[0], lv.n[1], lv.n[2], c->half,
+                                  c->cells + (size_t)c->line0[L] * kLineBytes, c->stream),
                 "packing sdf level");
         if (lv.albedo_rgb) {
             SDF_TRY(dev_alloc(&c->alb[L], 3 * cnt), "allocating albedo level");
@@ -2027,7 +2051,8 @@ struct sdfddgi_batch {
     std::vector<sdfddgi_batch_scene> scenes;
     std::vector<BatchScene> host_scenes;
     std::vector<BatchSet> sets;
-    void *quad[kMaxBatchScenes]{};
+    char *cells = nullptr;                   // cell bricks of every scene's grid
+    bool wide = false;                       // brick indices need 32-bit products
     float *alb[kMaxBatchScenes]{};
     // Frames are pipelined like the single-scene ones: the tables and primary trace
     // of frame f (the front graph, on the side stream) run beside frame f-1's hit
@@ -2080,9 +2105,9 @@ void batch_drop_graphs(sdfddgi_batch *b) {
 void batch_free(sdfddgi_batch *b) {
     batch_drop_graphs(b);
     for (int s = 0; s < kMaxBatchScenes; ++s) {
-        dev_free(b->quad[s]);
         dev_free(b->alb[s]);
     }
+    dev_free(b->cells);
     for (BatchSet &r : b->sets) {
         dev_free(r.base);
         for (int k = 0; k < 2; ++k) {
@@ -2113,6 +2138,8 @@ void batch_free(sdfddgi_batch *b) {
 BatchArgs batch_args(const sdfddgi_batch *b, int cur, int lane) {
     BatchArgs a{};
     a.nscenes = b->S;
+    a.cells = b->cells;
+    a.wide = b->wide ? 1 : 0;
     a.scenes = b->dev_scenes[lane];
     a.lights = reinterpret_cast<const float *>(b->frame_dev[lane] + 9 * sizeof(double));
     a.total_rays = (int)b->total_rays;
@@ -2373,13 +2400,24 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
     std::vector<int32_t> h_order((size_t)GP);
     std::vector<int2> h_blocks;
     b->host_scenes.resize(count);
+    int64_t lines = 0;
+    for (int s = 0; s < count; ++s) {
+        const int32_t *n = scenes[s].level.n;
+        const CellShape sh = cell_shape(n[0], n[1], n[2], true);
+        b->wide = b->wide || sh.wide;
+        lines += sh.lines();
+    }
+    if (lines >= (int64_t)1 << 32) return bail(lfail(SDFDDGI_ENOMEM, "grids too large together"));
+    b->wide = b->wide || lines * kLineBytes >= (int64_t)1 << 32;
+    B_TRY(dev_alloc(&b->cells, (size_t)lines * kLineBytes), "allocating the grids");
+    lines = 0;
     int64_t pbase = 0, rbase = 0;
     for (int s = 0; s < count; ++s) {
         const sdfddgi_batch_scene &sc = scenes[s];
         const sdfddgi_sdf_level &lv = sc.level;
-        const size_t nquad = (size_t)lv.n[0] * (lv.n[1] - 1) * (lv.n[2] - 1);
-        B_TRY(hipMalloc(&b->quad[s], nquad * 8), "allocating a grid");
-        B_TRY(launch_pack_quads(lv.sdf, lv.n[0], lv.n[1], lv.n[2], true, b->quad[s], b->stream),
+        const CellShape sh = cell_shape(lv.n[0], lv.n[1], lv.n[2], true);
+        B_TRY(launch_pack_cells(lv.sdf, lv.n[0], lv.n[1], lv.n[2], true,
+                                b->cells + (size_t)lines * kLineBytes, b->stream),
               "packing a grid");
         const size_t cnt = (size_t)lv.n[0] * lv.n[1] * lv.n[2];
         if (lv.albedo_rgb) {
@@ -2390,18 +2428,19 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
         }
         BatchScene &d = b->host_scenes[s];
         d = BatchScene{};
-        d.lv.quad = b->quad[s];
+        d.lv.line0 = (uint32_t)lines;
+        d.lv.nb0 = sh.nb0;
+        d.lv.nb1 = sh.nb1;
+        lines += sh.lines();
         d.lv.alb = b->alb[s];
         d.lv.org0 = (float)lv.origin[0];
         d.lv.org1 = (float)lv.origin[1];
         d.lv.org2 = (float)lv.origin[2];
         d.lv.inv = (float)(1.0 / lv.spacing);
-        d.lv.cmax0 = (float)(lv.n[0] - 2);
-        d.lv.cmax1 = (float)(lv.n[1] - 2);
-        d.lv.cmax2 = (float)(lv.n[2] - 2);
+        d.lv.cmax0 = (uint32_t)(lv.n[0] - 2);
+        d.lv.cmax1 = (uint32_t)(lv.n[1] - 2);
+        d.lv.cmax2 = (uint32_t)(lv.n[2] - 2);
         d.lv.half = (float)(0.5 * lv.spacing);
-        d.lv.row = (uint32_t)lv.n[0];
-        d.lv.slice = (uint32_t)lv.n[0] * (uint32_t)(lv.n[1] - 1);
         d.lv.arow = (uint32_t)lv.n[0];
         d.lv.aslice = (uint32_t)lv.n[0] * (uint32_t)lv.n[1];
         const float org[3] = {d.lv.org0, d.lv.org1, d.lv.org2};

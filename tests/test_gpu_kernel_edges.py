@@ -1,13 +1,17 @@
-"""The device baker and the map read-back at the sizes where their tilings can go
-wrong: grids thinner and longer than a brick, ragged bricks, primitive counts around
-the staging chunk, equal and non-finite primitives; maps whose float counts are not
-multiples of four."""
+"""The device baker, the map read-back and the trace at the sizes where their tilings
+can go wrong: grids thinner and longer than a brick, ragged bricks, primitive counts
+around the staging chunk, equal and non-finite primitives; maps whose float counts are
+not multiples of four; grids at the edges of the trace's cell bricks, too long for its
+24-bit products, and levels that are not nested."""
 import sys
 
 import numpy as np
 import pytest
 
+import oracle
 import scenegen
+from scenegen import Params, Primitives, ProbeGrid, SDFLevel, Workload
+from tests.helpers import fp16_grid, frame
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +79,68 @@ def test_maps_read_back_as_installed(S, res, offset):
         assert torch.equal(view, t)
         assert int((room == -1.0).sum()) == 8
     S.sdfddgi_destroy(ctx)
+
+
+def random_level(n, origin, spacing, seed):
+    """Distances of no scene: any value a sample may meet, few of them hits."""
+    rng = np.random.default_rng(seed)
+    sdf = (rng.uniform(0.02, 0.3, n[::-1]) * np.exp(rng.normal(size=n[::-1]))).astype(np.float32)
+    sdf[rng.random(sdf.shape) < 0.03] = -0.2
+    return SDFLevel(n=n, origin=origin, spacing=spacing, sdf=sdf, albedo=None)
+
+
+def trace_workload(levels, probes, rays, t_max=30.0):
+    none = Primitives(np.zeros(0, np.int32), np.zeros((0, 3)), np.zeros((0, 3)), np.zeros((0, 3)))
+    return Workload("edges", none, levels, probes,
+                    Params(rays_per_probe=rays, t_max=t_max, max_steps=24, hit_eps=5e-3), [])
+
+
+def check_trace(S, w, half):
+    import torch
+    ref = fp16_grid(w) if half else w
+    fr = frame((0.3, 1.0, 0.2), seed=77)
+    ctx = S.context_from_workload(w, flags=S.SDFDDGI_FLAG_RECORD_RAYS |
+                                  (S.SDFDDGI_FLAG_FP16 if half else 0))
+    S.sdfddgi_update_frame(ctx, fr.dir_to_light, fr.radiance_rgb, fr.rotation_seed)
+    rec = S.sdfddgi_get_ray_records(ctx).cpu().numpy()
+    torch.cuda.synchronize()
+    S.sdfddgi_destroy(ctx)
+    chk = oracle.Checker(ref)
+    irr0, dep0 = (np.zeros(s, np.float32) for s in scenegen.atlas_shapes(w.num_probes, w.params))
+    _, _, _, ref_rec = chk.update_probes(fr, True, irr0, dep0, want_records=True)
+    assert np.array_equal(rec, ref_rec)
+    return ref_rec
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("n", [(2, 2, 2), (4, 4, 4), (5, 4, 3), (3, 8, 5), (13, 6, 10),
+                               (66001, 3, 2), (2, 66001, 3), (3, 2, 66001)])
+def test_trace_at_brick_edges(S, n, half):
+    announce(f"trace on a {n} grid, half={half}")
+    spacing = 0.25
+    origin = (-1.0, 0.5, -2.0)
+    ext = [spacing * (k - 1) for k in n]
+    probes = ProbeGrid((3, 2, 3), tuple(o + 0.05 * min(e, 40.0) for o, e in zip(origin, ext)),
+                       tuple(0.4 * min(e, 40.0) for e in ext))
+    for rays in (16, 48):
+        check_trace(S, trace_workload([random_level(n, origin, spacing, sum(n))], probes, rays),
+                    half)
+
+
+@pytest.mark.parametrize("half", [False, True])
+def test_trace_through_levels_that_are_not_nested(S, half):
+    announce(f"levels sticking out of the next coarser one, half={half}")
+    levels = [random_level((9, 9, 9), (-1.0, -1.0, -1.0), 0.25, 5),
+              random_level((10, 6, 10), (-0.5, -1.5, -1.5), 0.4, 6),     # cuts level 0's corner
+              random_level((11, 12, 9), (-3.0, -3.0, -3.0), 0.55, 7)]
+    probes = ProbeGrid((4, 3, 4), (-2.0, -2.0, -2.0), (0.9, 1.1, 0.9))
+    rec = check_trace(S, trace_workload(levels, probes, 64), half)
+    assert set(np.unique(rec[..., 0] >> 8)) >= {0, 1, 2}
+
+
+@pytest.mark.parametrize("probes,rays", [((2, 2, 2), 16), ((5, 3, 7), 1008), ((17, 9, 11), 176)])
+def test_trace_covers_every_ray(S, probes, rays):
+    # the ray queue's claims: fewer rays than a wave, runs across probes, whole probes
+    announce(f"{probes} probes x {rays} rays")
+    w = scenegen.small_cascade(3, probes=probes, rays=rays)
+    check_trace(S, w, False)
