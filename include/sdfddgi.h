@@ -451,8 +451,8 @@ sdfddgi_status sdfddgi_bake_sdf_noalloc(int32_t nprims, const int32_t *kind, con
  * Many independent scenes of uneven size updated together: each frame is one
  * replay of a captured HIP graph whose launches cover every scene -- the ray
  * tables of each distinct ray count, one persistent primary trace over the
- * concatenated rays of all scenes, one hit-shading pass over all their hits and
- * one blend over all their probes. Every scene runs the precision form (its grid
+ * concatenated rays of all scenes, one hit-shading pass over all their hits, its
+ * multi-bounce lookups and one blend over all their probes. Every scene runs the precision form (its grid
  * stored in binary16, FP16/BF16 MFMA blend) of the update above, so each scene's
  * maps are bit-identical to a single-scene context created with
  * SDFDDGI_FLAG_FP16 and run over the same frames. Scenes share the frame's
@@ -491,10 +491,10 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
                                     void *hip_stream, sdfddgi_batch **out);
 
 /* One frame for every scene: lights (host [count]) and the shared rotation seed.
- * Enqueues two graph replays: the tables and primary trace on a side stream of
- * the batch (default priority) and the hit shading and blend on the batch's
- * stream, joined by an event. Consecutive calls overlap (a frame's side part runs
- * beside the previous frame's hit shading and blend); any other call on the batch
+ * Enqueues two graph replays: the tables, the primary trace and the atlas-independent
+ * half of the hit shading on a side stream of the batch (default priority) and the
+ * lookups and blend on the batch's stream, joined by an event. Consecutive calls overlap
+ * (a frame's side part runs beside the previous frame's lookups and blend); any other call on the batch
  * in between makes the next frame wait for everything before it. Results are
  * valid once the caller synchronises the batch's stream. */
 sdfddgi_status sdfddgi_batch_update_frame(sdfddgi_batch *b, const sdfddgi_light *lights,

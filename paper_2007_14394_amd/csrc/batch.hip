@@ -4,7 +4,8 @@
 //   batch_begin_kernel    zero the counters, stamp the frame start on the device clock
 //   batch_primary_kernel  primary sphere trace of every scene's rays, one persistent
 //                         wave-compacted grid over the concatenated ray space
-//   batch_hits_kernel     hit shading of every scene's queued hits
+//   batch_hits_kernel     first half of every scene's hit shading (normal, shadow ray, albedo)
+//   batch_shade_kernel    second half (multi-bounce lookup, payload)
 //   batch_blend_kernel    the precision-form blend of every scene's probes, one
 //                         workgroup per 16 probes of a scene; stamps each scene's end
 //
@@ -15,6 +16,8 @@
 // scenes' first slots) or from the hit-queue entry; the fields the sample loop needs
 // are copied to registers when the lane takes the ray. The chunk sizes, refill
 // threshold and grid sizes are chosen by the runtime's autotuner.
+#include <algorithm>
+
 #include "internal.h"
 #include "octahedral.h"
 #include "trace_common.h"
@@ -41,33 +44,25 @@ __device__ __forceinline__ LaneScene lane_scene(const BatchScene &s) {
     return d;
 }
 
-// One sample of the fixed sphere-trace sequence (as trace_step of the single-scene
-// kernels with one level: a point inside the grid box is level 0, else the ray
-// escapes).
-template <bool kPrimary>
-__device__ __forceinline__ int batch_step(const BatchArgs &a, const LaneScene &d, float o0, float o1,
-                                          float o2, float w0, float w1, float w2, float &t, int &k,
-                                          int &steps) {
+// One sample of the fixed sphere-trace sequence for the lanes of `live` (as trace_step of
+// the single-scene kernels with one level: a point inside the grid box is level 0, else
+// the ray escapes); returns those whose ray goes on.
+template <bool kWide>
+__device__ __forceinline__ uint64_t batch_step(GlobalBytes cells, const LaneScene &d, uint64_t live,
+                                               float o0, float o1, float o2, float w0, float w1,
+                                               float w2, float &t, int &k, float &dist, int &level) {
     const float x0 = fmaf(t, w0, o0), x1 = fmaf(t, w1, o1), x2 = fmaf(t, w2, o2);
     const bool box = (x0 >= d.xlo0) & (x0 <= d.xhi0) & (x1 >= d.xlo1) & (x1 <= d.xhi1) &
                      (x2 >= d.xlo2) & (x2 <= d.xhi2);
-    const bool over = t > d.t_max;
-    const bool in = box && !over;
-    float dist = 0.0f;
-    if (a.wide) {
-        if (in) dist = distance_inside<true, true>((GlobalBytes)a.cells, d.lv, x0, x1, x2);
-    } else {
-        if (in) dist = distance_inside<true, false>((GlobalBytes)a.cells, d.lv, x0, x1, x2);
+    const uint64_t inside = live & __ballot(box) & ~__ballot(t > d.t_max);
+    level = in_mask(live) ? (box ? 0 : -1) : level;
+    if (in_mask(inside)) dist = distance_inside<true, kWide>(cells, d.lv, x0, x1, x2);
+    const uint64_t go = inside & ~__ballot(dist < d.eps) & ~__ballot(k + 1 == d.max_steps);
+    if (in_mask(go)) {
+        t = fmaf(d.relax, dist, t);
+        ++k;
     }
-    const bool inside = kPrimary && k == 0 && dist < 0.0f;
-    const bool hit = dist < d.eps;
-    const bool last = k + 1 == d.max_steps;
-    int kind = inside ? kInside : hit ? kHit : last ? kHitExhausted : -1;
-    kind = over ? kMissTmax : !box ? kMissExit : kind;
-    steps = in ? k + 1 : k;
-    t = in && !inside && !hit ? fmaf(d.relax, dist, t) : t;
-    ++k;
-    return kind;
+    return go;
 }
 
 __device__ __forceinline__ void load_scenes(const BatchArgs &a, BatchScene *s_sc, int *s_base) {
@@ -109,93 +104,130 @@ __device__ __forceinline__ void batch_flush(const BatchArgs &a, int4 *buf, int c
 }
 
 // Primary trace over the concatenated rays of all scenes (see primary_kernel).
-template <int kChunkSize>
-__global__ __launch_bounds__(256) void batch_primary_kernel(BatchArgs a) {
+template <bool kWide>
+__global__ __launch_bounds__(256) void batch_primary_kernel(BatchArgs a, int chunk) {
+    constexpr int kQueue = 128;
     __shared__ BatchScene s_sc[kMaxBatchScenes];
     __shared__ int s_base[kMaxBatchScenes];
     __shared__ int4 s_hits[4][64];
+    __shared__ WaitingRay s_rays[4][kQueue];   // origin and scene, direction and ray
     load_scenes(a, s_sc, s_base);
+    const GlobalBytes cells = (GlobalBytes)a.cells;
     const int lane = (int)__lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int staged = 0;
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     // blocks of the concatenated rays dealt to the XCDs in turn (see BlockFeeder)
-    BlockFeeder feed(kChunkSize, kBatchBlockRays / kChunkSize);
-    bool active = false;
-    int ray = 0, k = 0, sc = 0;
-    float o0 = 0, o1 = 0, o2 = 0, w0 = 0, w1 = 0, w2 = 0, t = 0;
+    BlockFeeder feed(chunk, kBatchBlockRays / chunk);
+    uint64_t live = 0, ended = 0;
+    int staged = 0, head = 0, waiting = 0, stage = 0, coming = 0;
+    int ray = 0, k = 0, sc = 0, level = 0, n_ray = 0, n_probe = 0, n_sc = 0;
+    float o0 = 0, o1 = 0, o2 = 0, w0 = 0, w1 = 0, w2 = 0, t = 0, dist = 0;
+    float m0 = 0, m1 = 0, m2 = 0, v0 = 0, v1 = 0, v2 = 0;
     LaneScene d{};
     while (true) {
-        uint64_t stepping = __ballot(active);
-        if (__popcll(stepping) < a.refill) {
-            uint64_t idle = ~stepping;
-            while (idle != 0 && !feed.exhausted) {
-                int first = 0;
-                const int n = feed.claim(a.counter + kPartStride, a.total_rays, __popcll(idle), first);
-                const int rank = __popcll(idle & below);
-                if (!active && rank < n) {
-                    const int slot = first + rank;
-                    sc = scene_of(s_base, a.nscenes, slot);
-                    const BatchScene &s = s_sc[sc];
-                    const int local = slot - s.ray_base;
-                    const int q = local / s.R, i = local - q * s.R;
-                    const int p = a.probe_order[s.probe_base + q];
-                    ray = s.ray_base + p * s.R + i;
-                    const int gp = s.probe_base + p;
-                    o0 = a.probe_pos[3 * gp]; o1 = a.probe_pos[3 * gp + 1]; o2 = a.probe_pos[3 * gp + 2];
-                    const int di = s.dir_base + i;
-                    w0 = a.dirs[3 * di]; w1 = a.dirs[3 * di + 1]; w2 = a.dirs[3 * di + 2];
-                    d = lane_scene(s);
+        if (stage == 2) {
+            if (lane < coming) {
+                WaitingRay &r = s_rays[wave][(head + waiting + lane) & (kQueue - 1)];
+                r.from = make_float4(m0, m1, m2, __int_as_float(n_sc));
+                r.dir = make_float4(v0, v1, v2, __int_as_float(n_ray));
+            }
+            __builtin_amdgcn_wave_barrier();
+            waiting += coming;
+            stage = 0;
+        } else if (stage == 1) {
+            if (lane < coming) {
+                const BatchScene &s = s_sc[n_sc];
+                n_ray += s.ray_base + n_probe * s.R;
+                const int gp = s.probe_base + n_probe;
+                m0 = a.probe_pos[3 * gp]; m1 = a.probe_pos[3 * gp + 1]; m2 = a.probe_pos[3 * gp + 2];
+            }
+            stage = 2;
+        }
+        if (__popcll(live) < a.refill) {
+            if (ended) {
+                bool hit = false;
+                int4 entry = make_int4(0, 0, 0, 0);
+                if (in_mask(ended)) {
+                    const bool over = t > d.t_max, out = over || level < 0;
+                    const bool inside = !out && k == 0 && dist < 0.0f;
+                    if (out || inside) {
+                        const BatchScene &s = s_sc[sc];
+                        a.payload[ray] = inside ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
+                                                : make_float4(s.sky0, s.sky1, s.sky2, s.t_max);
+                    } else {
+                        hit = true;
+                        entry = make_int4(ray, __float_as_int(t),
+                                          pack_hit(dist < d.eps ? kHit : kHitExhausted, 0, k + 1),
+                                          sc);
+                    }
+                }
+                ended = 0;
+                const uint64_t hm = __ballot(hit);
+                if (hm) {
+                    const int n = __popcll(hm);
+                    if (staged + n > 64) {
+                        batch_flush(a, s_hits[wave], staged);
+                        staged = 0;
+                    }
+                    if (hit) s_hits[wave][staged + __popcll(hm & below)] = entry;
+                    __builtin_amdgcn_wave_barrier();
+                    staged += n;
+                }
+            }
+            if (waiting > 0) {
+                const int rank = __popcll(~live & below);
+                const uint64_t take = __ballot(in_mask(~live) && rank < waiting);
+                if (in_mask(take)) {
+                    const WaitingRay r = s_rays[wave][(head + rank) & (kQueue - 1)];
+                    o0 = r.from.x; o1 = r.from.y; o2 = r.from.z;
+                    w0 = r.dir.x; w1 = r.dir.y; w2 = r.dir.z;
+                    sc = __float_as_int(r.from.w);
+                    ray = __float_as_int(r.dir.w);
+                    d = lane_scene(s_sc[sc]);
                     t = 0.0f;
                     k = 0;
-                    active = true;
                 }
-                idle = __ballot(!active);
+                __builtin_amdgcn_wave_barrier();
+                live |= take;
+                const int n = __popcll(take);
+                head += n;
+                waiting -= n;
             }
-            stepping = __ballot(active);
-            if (stepping == 0) {
-                batch_flush(a, s_hits[wave], staged);
-                break;
-            }
-        }
-        bool hit_now = false;
-        int4 entry = make_int4(0, 0, 0, 0);
-        if (active) {
-            const float tt = t;
-            int steps = 0;
-            const int kind = batch_step<true>(a, d, o0, o1, o2, w0, w1, w2, t, k, steps);
-            if (kind >= 0) {
-                if (kind == kHit || kind == kHitExhausted) {
-                    hit_now = true;
-                    entry = make_int4(ray, __float_as_int(tt), pack_hit(kind, 0, steps), sc);
-                } else {
-                    const BatchScene &s = s_sc[sc];
-                    a.payload[ray] = kind == kInside ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
-                                                     : make_float4(s.sky0, s.sky1, s.sky2, s.t_max);
+            if (stage == 0 && !feed.exhausted && waiting <= kQueue - 64 - 16) {
+                coming = 0;
+                while (coming < 64 && !feed.exhausted) {
+                    int first = 0;
+                    const int n = feed.claim(a.counter + kPartStride, a.total_rays, 64 - coming,
+                                             first);
+                    if (lane >= coming && lane < coming + n) {
+                        const int slot = first + lane - coming;
+                        n_sc = scene_of(s_base, a.nscenes, slot);
+                        const BatchScene &s = s_sc[n_sc];
+                        const int local = slot - s.ray_base;
+                        const int q = local / s.R;
+                        n_ray = local - q * s.R;
+                        n_probe = a.probe_order[s.probe_base + q];
+                        const int di = s.dir_base + n_ray;
+                        v0 = a.dirs[3 * di]; v1 = a.dirs[3 * di + 1]; v2 = a.dirs[3 * di + 2];
+                    }
+                    coming += n;
                 }
-                active = false;
+                stage = coming ? 1 : 0;
+            }
+            if (!live) {
+                if (stage == 0 && feed.exhausted) {
+                    batch_flush(a, s_hits[wave], staged);
+                    break;
+                }
+                continue;
             }
         }
-        const uint64_t hm = __ballot(hit_now);
-        if (hm) {
-            const int n = __popcll(hm);
-            if (staged + n > 64) {
-                batch_flush(a, s_hits[wave], staged);
-                staged = 0;
-            }
-            if (hit_now) s_hits[wave][staged + __popcll(hm & below)] = entry;
-            __builtin_amdgcn_wave_barrier();
-            staged += n;
-            if (staged == 64) {
-                batch_flush(a, s_hits[wave], staged);
-                staged = 0;
-            }
-        }
+        const uint64_t go = batch_step<kWide>(cells, d, live, o0, o1, o2, w0, w1, w2, t, k, dist,
+                                              level);
+        ended |= live & ~go;
+        live = go;
     }
 }
-
-enum : int { kBIdle = 0, kBShadow = 1, kBNew = 2, kBPendShade = 3 };
-constexpr int kBShadeBatch = 16;
 
 __device__ __forceinline__ float3 batch_albedo(const BatchScene &s, float x0, float x1, float x2) {
     const LevelLds &d = s.lv;
@@ -221,111 +253,154 @@ __device__ __forceinline__ float3 batch_albedo(const BatchScene &s, float x0, fl
     return make_float3(out[0], out[1], out[2]);
 }
 
-// Hit shading of every scene's queued hits (see hits_kernel).
-template <int kChunkSize>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void batch_hits_kernel(BatchArgs a) {
+// First half of hit shading for every scene's queued hits (see hits_kernel).
+template <bool kWide>
+__global__ __launch_bounds__(256) void batch_hits_kernel(BatchArgs a, int chunk) {
+    constexpr int kQueue = 128;
+    __shared__ BatchScene s_sc[kMaxBatchScenes];
+    __shared__ int s_base[kMaxBatchScenes];
+    __shared__ float4 s_rays[4][kQueue];   // shadow ray origins, hit-queue indices
+    __shared__ int s_ray_sc[4][kQueue];    // their scenes
+    load_scenes(a, s_sc, s_base);
+    const GlobalBytes cells = (GlobalBytes)a.cells;
+    const int lane = (int)__lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int total = __builtin_amdgcn_readfirstlane(a.counter[2]);
+    Feeder feed(chunk);
+    uint64_t live = 0, ended = 0;
+    int head = 0, waiting = 0, stage = 0, coming = 0;
+    int qi = 0, k = 0, level = 0, n_qi = 0;
+    float o0 = 0, o1 = 0, o2 = 0, t = 0, dist = 0, l0 = 0, l1 = 0, l2 = 0;
+    int4 e = make_int4(0, 0, 0, 0);
+    float p0 = 0, p1 = 0, p2 = 0, w0 = 0, w1 = 0, w2 = 0;
+    LaneScene d{};
+    while (true) {
+        if (stage == 2) {
+            bool lit = false;
+            float4 from = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (lane < coming) {
+                const BatchScene &s = s_sc[e.w];
+                const float *lt = a.lights + 6 * e.w;
+                const float ht = __int_as_float(e.y);
+                const float x0 = fmaf(ht, w0, p0), x1 = fmaf(ht, w1, p1), x2 = fmaf(ht, w2, p2);
+                const float3 alb = batch_albedo(s, x0, x1, x2);
+                float n0, n1, n2;
+                hit_normal<true>(cells, s.lv, kWide, x0, x1, x2, w0, w1, w2, n0, n1, n2);
+                const float ndl = fmaf(n2, lt[2], fmaf(n1, lt[1], n0 * lt[0]));
+                lit = ndl > 0.0f;
+                const int64_t at = 2 * (int64_t)n_qi;
+                a.geo[at] = make_float4(n0, n1, n2, lit ? ndl : 0.0f);
+                a.geo[at + 1] = make_float4(alb.x, alb.y, alb.z, 0.0f);
+                from = make_float4(fmaf(n0, s.bias, x0), fmaf(n1, s.bias, x1),
+                                   fmaf(n2, s.bias, x2), __int_as_float(n_qi));
+            }
+            const uint64_t m = __ballot(lit);
+            if (lit) {
+                const int at = (head + waiting + __popcll(m & below)) & (kQueue - 1);
+                s_rays[wave][at] = from;
+                s_ray_sc[wave][at] = e.w;
+            }
+            __builtin_amdgcn_wave_barrier();
+            waiting += __popcll(m);
+            stage = 0;
+        } else if (stage == 1) {
+            if (lane < coming) {
+                const BatchScene &s = s_sc[e.w];
+                const int local = e.x - s.ray_base;
+                const int p = local / s.R, i = local - p * s.R;
+                const int gp = s.probe_base + p, di = s.dir_base + i;
+                p0 = a.probe_pos[3 * gp]; p1 = a.probe_pos[3 * gp + 1]; p2 = a.probe_pos[3 * gp + 2];
+                w0 = a.dirs[3 * di]; w1 = a.dirs[3 * di + 1]; w2 = a.dirs[3 * di + 2];
+            }
+            stage = 2;
+        }
+        if (__popcll(live) < a.refill) {
+            if (ended) {
+                // stopped inside the grid before t_max: at a hit or out of steps
+                if (in_mask(ended) && !(t > d.t_max) && level >= 0)
+                    a.geo[2 * (int64_t)qi].w = 0.0f;
+                ended = 0;
+            }
+            if (waiting > 0) {
+                const int rank = __popcll(~live & below);
+                const uint64_t take = __ballot(in_mask(~live) && rank < waiting);
+                if (in_mask(take)) {
+                    const int at = (head + rank) & (kQueue - 1);
+                    const float4 r = s_rays[wave][at];
+                    const int sc = s_ray_sc[wave][at];
+                    o0 = r.x; o1 = r.y; o2 = r.z;
+                    qi = __float_as_int(r.w);
+                    const float *lt = a.lights + 6 * sc;
+                    l0 = lt[0]; l1 = lt[1]; l2 = lt[2];
+                    d = lane_scene(s_sc[sc]);
+                    t = 0.0f;
+                    k = 0;
+                }
+                __builtin_amdgcn_wave_barrier();
+                live |= take;
+                const int n = __popcll(take);
+                head += n;
+                waiting -= n;
+            }
+            if (stage == 0 && !feed.exhausted && waiting <= kQueue - 64 - 16) {
+                coming = 0;
+                while (coming < 64 && !feed.exhausted) {
+                    int first = 0;
+                    const int n = feed.claim(a.counter + 1, total, 64 - coming, first);
+                    if (lane >= coming && lane < coming + n) {
+                        n_qi = first + lane - coming;
+                        e = a.hitq[n_qi];
+                    }
+                    coming += n;
+                }
+                stage = coming ? 1 : 0;
+            }
+            if (!live) {
+                if (stage == 0 && feed.exhausted && waiting == 0) break;
+                continue;
+            }
+        }
+        const uint64_t go = batch_step<kWide>(cells, d, live, o0, o1, o2, l0, l1, l2, t, k, dist,
+                                              level);
+        ended |= live & ~go;
+        live = go;
+    }
+}
+
+// Second half of hit shading: the multi-bounce lookup and the payload of every scene's
+// queued hits (see shade_kernel).
+__global__ __launch_bounds__(256) void batch_shade_kernel(BatchArgs a) {
     __shared__ BatchScene s_sc[kMaxBatchScenes];
     __shared__ int s_base[kMaxBatchScenes];
     load_scenes(a, s_sc, s_base);
-    const int lane = (int)__lane_id();
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const int total = a.counter[2];
-    Feeder<kChunkSize> feed;
     const int tile = 10 * 10 * 3;   // 8x8 irradiance tile with its border
-
-    int mode = kBIdle, ray = 0, info = 0, k = 0, vis = -1, sc = 0;
-    float ht = 0, hx0 = 0, hx1 = 0, hx2 = 0, n0 = 0, n1 = 0, n2 = 0;
-    float o0 = 0, o1 = 0, o2 = 0, t = 0, l0 = 0, l1 = 0, l2 = 0;
-    LaneScene d{};
-    while (true) {
-        uint64_t stepping = __ballot(mode == kBShadow);
-        const int waiting = __popcll(__ballot(mode == kBPendShade));
-        if (__popcll(stepping) < a.refill || waiting >= kBShadeBatch) {
-            for (int round = 0; round < 2; ++round) {
-                if (__ballot(mode == kBPendShade)) {
-                    if (mode == kBPendShade) {
-                        const BatchScene &s = s_sc[sc];
-                        const float *lt = a.lights + 6 * sc;
-                        const float ndl = fmaf(n2, l2, fmaf(n1, l1, n0 * l0));
-                        const float lit = vis == 1 ? ndl : 0.0f;
-                        const float3 alb = batch_albedo(s, hx0, hx1, hx2);
-                        float3 ind = make_float3(0.0f, 0.0f, 0.0f);
-                        if (s.gain != 0.0f)
-                            ind = interp_irradiance(a.prev_irr + (size_t)s.probe_base * tile, 8,
-                                                    s.pg, hx0, hx1, hx2, n0, n1, n2);
-                        const float inv_pi = 0.318309886183790671538f;
-                        float4 out;
-                        out.x = alb.x * inv_pi * (lt[3] * lit + s.gain * ind.x);
-                        out.y = alb.y * inv_pi * (lt[4] * lit + s.gain * ind.y);
-                        out.z = alb.z * inv_pi * (lt[5] * lit + s.gain * ind.z);
-                        out.w = ht;
-                        a.payload[ray] = out;
-                        mode = kBIdle;
-                    }
-                }
-                if (round == 1) break;
-                uint64_t idle = __ballot(mode == kBIdle);
-                while (idle != 0 && !feed.exhausted) {
-                    int first = 0;
-                    const int n = feed.claim(a.counter + 1, total, __popcll(idle), first);
-                    const int rank = __popcll(idle & below);
-                    if (mode == kBIdle && rank < n) {
-                        const int4 e = a.hitq[first + rank];
-                        ray = e.x;
-                        ht = __int_as_float(e.y);
-                        info = e.z;
-                        sc = e.w;
-                        mode = kBNew;
-                    }
-                    idle = __ballot(mode == kBIdle);
-                }
-                if (__ballot(mode == kBNew)) {
-                    if (mode == kBNew) {
-                        const BatchScene &s = s_sc[sc];
-                        const int local = ray - s.ray_base;
-                        const int p = local / s.R, i = local - (local / s.R) * s.R;
-                        const int gp = s.probe_base + p;
-                        const float po0 = a.probe_pos[3 * gp], po1 = a.probe_pos[3 * gp + 1],
-                                    po2 = a.probe_pos[3 * gp + 2];
-                        const int di = s.dir_base + i;
-                        const float w0 = a.dirs[3 * di], w1 = a.dirs[3 * di + 1],
-                                    w2 = a.dirs[3 * di + 2];
-                        const float *lt = a.lights + 6 * sc;
-                        l0 = lt[0]; l1 = lt[1]; l2 = lt[2];
-                        hx0 = fmaf(ht, w0, po0); hx1 = fmaf(ht, w1, po1); hx2 = fmaf(ht, w2, po2);
-                        hit_normal<true, 1>((GlobalBytes)a.cells, s.lv, a.wide, hx0, hx1, hx2, w0, w1, w2, n0, n1,
-                                         n2);
-                        const float ndl = fmaf(n2, l2, fmaf(n1, l1, n0 * l0));
-                        if (ndl > 0.0f) {
-                            o0 = fmaf(n0, s.bias, hx0);
-                            o1 = fmaf(n1, s.bias, hx1);
-                            o2 = fmaf(n2, s.bias, hx2);
-                            d = lane_scene(s);
-                            t = 0.0f;
-                            k = 0;
-                            mode = kBShadow;
-                        } else {
-                            vis = -1;
-                            k = 0;
-                            mode = kBPendShade;
-                        }
-                    }
-                }
-            }
-            stepping = __ballot(mode == kBShadow);
-            if (stepping == 0 && feed.exhausted) break;
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < total; q += gridDim.x * blockDim.x) {
+        const int4 e = a.hitq[q];
+        const float4 g0 = a.geo[2 * (int64_t)q], g1 = a.geo[2 * (int64_t)q + 1];
+        const BatchScene &s = s_sc[e.w];
+        const float *lt = a.lights + 6 * e.w;
+        const float ht = __int_as_float(e.y);
+        float3 ind = make_float3(0.0f, 0.0f, 0.0f);
+        if (s.gain != 0.0f) {
+            const int local = e.x - s.ray_base;
+            const int p = local / s.R, i = local - p * s.R;
+            const int gp = s.probe_base + p, di = s.dir_base + i;
+            const float x0 = fmaf(ht, a.dirs[3 * di], a.probe_pos[3 * gp]);
+            const float x1 = fmaf(ht, a.dirs[3 * di + 1], a.probe_pos[3 * gp + 1]);
+            const float x2 = fmaf(ht, a.dirs[3 * di + 2], a.probe_pos[3 * gp + 2]);
+            ind = interp_irradiance(a.prev_irr + (size_t)s.probe_base * tile, 8, s.pg, x0, x1, x2,
+                                    g0.x, g0.y, g0.z);
         }
-        if (mode == kBShadow) {
-            int steps = 0;
-            const int kind = batch_step<false>(a, d, o0, o1, o2, l0, l1, l2, t, k, steps);
-            if (kind >= 0) {
-                vis = (kind == kHit || kind == kHitExhausted) ? 0 : 1;
-                k = steps;
-                mode = kBPendShade;
-            }
-        }
+        const float inv_pi = 0.318309886183790671538f;
+        float4 out;
+        out.x = g1.x * inv_pi * (lt[3] * g0.w + s.gain * ind.x);
+        out.y = g1.y * inv_pi * (lt[4] * g0.w + s.gain * ind.y);
+        out.z = g1.z * inv_pi * (lt[5] * g0.w + s.gain * ind.z);
+        out.w = ht;
+        a.payload[e.x] = out;
     }
-    (void)info;
 }
 
 // One workgroup per kP probes of one scene (16 / kP workgroups per entry of the
@@ -365,32 +440,28 @@ __global__ __launch_bounds__(256) void batch_blend_kernel(BatchBlendArgs b) {
 
 // ---------------------------------------------------------------- launchers --
 
-template <int kChunk>
-static hipError_t launch_primary_chunk(const BatchArgs &a, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(batch_primary_kernel<kChunk>, dim3(blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-template <int kChunk>
-static hipError_t launch_hits_chunk(const BatchArgs &a, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(batch_hits_kernel<kChunk>, dim3(blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
 bool batch_chunk_supported(int chunk, bool hits) {
     if (hits) return chunk == 16 || chunk == 32 || chunk == 64 || chunk == 128;
     return chunk == 64 || chunk == 128 || chunk == 256 || chunk == 512;
 }
 
-int batch_max_blocks(int device, bool hits) {
-    int per_cu = 0, cus = 0;
-    const void *k = hits ? (const void *)batch_hits_kernel<64> : (const void *)batch_primary_kernel<256>;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
+static int device_cus(int device) {
+    int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         cus < 1)
         cus = 256;
-    return per_cu * cus;
+    return cus;
+}
+
+int batch_max_blocks(int device, bool hits) { return (hits ? 4 : 8) * device_cus(device); }
+
+int batch_resident_blocks(int device, bool hits) {
+    int per_cu = 0;
+    const void *k = hits ? (const void *)batch_hits_kernel<false>
+                         : (const void *)batch_primary_kernel<false>;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    return std::min(per_cu * device_cus(device), batch_max_blocks(device, hits));
 }
 
 hipError_t launch_batch_begin(int *counter, unsigned long long *stamps, int n, hipStream_t s) {
@@ -399,23 +470,31 @@ hipError_t launch_batch_begin(int *counter, unsigned long long *stamps, int n, h
 }
 
 hipError_t launch_batch_primary(const BatchArgs &a, const BatchTuning &t, hipStream_t s) {
-    switch (t.primary_chunk) {
-        case 64: return launch_primary_chunk<64>(a, t.primary_blocks, s);
-        case 128: return launch_primary_chunk<128>(a, t.primary_blocks, s);
-        case 256: return launch_primary_chunk<256>(a, t.primary_blocks, s);
-        case 512: return launch_primary_chunk<512>(a, t.primary_blocks, s);
-        default: return hipErrorInvalidValue;
-    }
+    if (a.wide)
+        hipLaunchKernelGGL(batch_primary_kernel<true>, dim3(t.primary_blocks), dim3(256), 0, s, a,
+                           t.primary_chunk);
+    else
+        hipLaunchKernelGGL(batch_primary_kernel<false>, dim3(t.primary_blocks), dim3(256), 0, s, a,
+                           t.primary_chunk);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_hits(const BatchArgs &a, const BatchTuning &t, hipStream_t s) {
-    switch (t.hits_chunk) {
-        case 16: return launch_hits_chunk<16>(a, t.hits_blocks, s);
-        case 32: return launch_hits_chunk<32>(a, t.hits_blocks, s);
-        case 64: return launch_hits_chunk<64>(a, t.hits_blocks, s);
-        case 128: return launch_hits_chunk<128>(a, t.hits_blocks, s);
-        default: return hipErrorInvalidValue;
-    }
+    if (a.wide)
+        hipLaunchKernelGGL(batch_hits_kernel<true>, dim3(t.hits_blocks), dim3(256), 0, s, a,
+                           t.hits_chunk);
+    else
+        hipLaunchKernelGGL(batch_hits_kernel<false>, dim3(t.hits_blocks), dim3(256), 0, s, a,
+                           t.hits_chunk);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_shade(const BatchArgs &a, hipStream_t s) {
+    // four workgroups per CU of the 256-CU part, striding over the queue
+    const int64_t blocks = ((int64_t)a.total_rays + 255) / 256;
+    hipLaunchKernelGGL(batch_shade_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256),
+                       0, s, a);
+    return hipGetLastError();
 }
 
 template <int kP, int kChunk>

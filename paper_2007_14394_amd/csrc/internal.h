@@ -104,11 +104,10 @@ struct TraceArgs {
     int analytic;               // 1: distances from the primitives in `an`, not the grid
     AnalyticArgs an;
     const float *prim_alb;      // [nprims][3] albedo of each primitive, cluster order
-    float4 *geo;                // null: hits_kernel shades each hit. Else hit shading is split:
-                                //     hits_kernel stores, per hit-queue entry i, what does not
-                                //     depend on the previous atlas -- geo[2i] = (normal, sun
+    float4 *geo;                // [P*R][2]: hits_kernel stores, per hit-queue entry i, what does
+                                //     not depend on the previous atlas -- geo[2i] = (normal, sun
                                 //     term n.l or 0 in shadow), geo[2i+1] = (albedo, 0) -- and
-                                //     shade_kernel adds the multi-bounce lookup later
+                                //     shade_kernel adds the multi-bounce lookup
 };
 
 struct TraceGrid {
@@ -173,7 +172,7 @@ hipError_t launch_tables_weights(TableArgs a, hipStream_t stream);
 TraceGrid trace_grid(int device, int64_t rays, bool half, bool analytic = false);
 hipError_t launch_primary(const TraceArgs &a, const TraceGrid &grid, hipStream_t stream);
 hipError_t launch_hits(const TraceArgs &a, const TraceGrid &grid, hipStream_t stream);
-// The atlas-dependent half of split hit shading (TraceArgs::geo): one thread per queue entry.
+// The atlas-dependent half of hit shading (TraceArgs::geo): one thread per queue entry.
 hipError_t launch_shade(const TraceArgs &a, hipStream_t stream);
 hipError_t launch_blend(const BlendArgs &a, hipStream_t stream);
 hipError_t launch_sample(const SampleArgs &a, hipStream_t stream);
@@ -364,6 +363,8 @@ struct BatchArgs {
     const float *prev_irr;                // [GP] irradiance tiles of the previous frame
     float4 *payload;                      // [total_rays]
     int4 *hitq;                           // [total_rays]: (ray, bits of t, info, scene)
+    float4 *geo;                          // [total_rays][2]: first half of the queued hits'
+                                          //     shading (see TraceArgs)
     int *counter;                         // [3]
     int refill;                           // refill idle lanes below this many stepping lanes
 };
@@ -389,12 +390,14 @@ hipError_t launch_batch_begin(int *counter, unsigned long long *stamps, int nsce
                               hipStream_t stream);
 hipError_t launch_batch_primary(const BatchArgs &a, const BatchTuning &t, hipStream_t stream);
 hipError_t launch_batch_hits(const BatchArgs &a, const BatchTuning &t, hipStream_t stream);
+hipError_t launch_batch_shade(const BatchArgs &a, hipStream_t stream);
 // nblocks16 entries of the 16-probe block table, each split into 16 / blend_probes
 // workgroups.
 hipError_t launch_batch_blend(const BatchBlendArgs &a, int nblocks16, const BatchTuning &t,
                               hipStream_t stream);
 bool batch_blend_tile_supported(int probes, int chunk);
-int batch_max_blocks(int device, bool hits);
+int batch_resident_blocks(int device, bool hits);   // workgroups that fit at once
+int batch_max_blocks(int device, bool hits);        // most that a tuning may ask for
 
 // -------------------------------------------------- analytic SDF (cluster.hip) --
 

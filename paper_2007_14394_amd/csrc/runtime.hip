@@ -117,7 +117,7 @@ struct RaySet {
     int4 *hitq = nullptr;            // [P][R]
     int *counter = nullptr;          // [kSetCounters] counters of the set's trace (see TraceArgs);
                                      //     [6] the length of `list`
-    float4 *geo = nullptr;           // learned form: [P][R][2] split hit shading (TraceArgs::geo)
+    float4 *geo = nullptr;           // [P][R][2] hit shading's first half (TraceArgs::geo)
     int *list = nullptr;             // learned form's fallback sets: [P] the frame's fallback list
     TraceGrid grid;
     hipEvent_t done = nullptr;       // main / spare: recorded on the caller's stream once the
@@ -617,7 +617,7 @@ ProbeGridDev dev_probes(const sdfddgi_ctx *c) {
 
 // Allocate a ray set of R rays: the fixed spherical-Fibonacci set (binary64,
 // uploaded), zeroed weight tables and the per-ray buffers.
-hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool split = false) {
+hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool listed = false) {
     free_set(r);
     r.R = R;
     std::vector<double> h_base(3 * (size_t)R);
@@ -633,10 +633,8 @@ hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool split = false) {
     chk(dev_alloc(&r.payload, (size_t)c->P * R));
     chk(dev_alloc(&r.hitq, (size_t)c->P * R));
     chk(dev_alloc(&r.counter, kSetCounters));
-    if (split) {
-        chk(dev_alloc(&r.geo, 2 * (size_t)c->P * R));
-        chk(dev_alloc(&r.list, (size_t)c->P));
-    }
+    chk(dev_alloc(&r.geo, 2 * (size_t)c->P * R));
+    if (listed) chk(dev_alloc(&r.list, (size_t)c->P));
     if (e != hipSuccess) return e;
     chk(hipMemcpy(r.base, h_base.data(), 3 * (size_t)R * sizeof(double), hipMemcpyHostToDevice));
     chk(hipMemsetAsync(r.wt_i, 0, (size_t)R * c->Tpi * sizeof(float), c->stream));
@@ -765,6 +763,7 @@ TraceArgs trace_pass(const TraceArgs &base, const RaySet &r, int *counters, int 
     t.dirs = r.dirs;
     t.payload = r.payload;
     t.hitq = r.hitq;
+    t.geo = r.geo;
     t.counter = counters;
     t.records = records;
     if (list) {
@@ -1020,11 +1019,8 @@ static sdfddgi_status create_ctx(const sdfddgi_sdf_grid *sdf, const HostClusters
     }
     SDF_TRY(ce, "uploading constants");
 
-    // the grid backends split the pipelined frames' hit shading (geometry records)
-    SDF_TRY(alloc_set(c, c->main, params->rays_per_probe, !c->analytic),
-            "allocating the ray set");
-    SDF_TRY(alloc_set(c, c->spare, params->rays_per_probe, !c->analytic),
-            "allocating the ray set");
+    SDF_TRY(alloc_set(c, c->main, params->rays_per_probe), "allocating the ray set");
+    SDF_TRY(alloc_set(c, c->spare, params->rays_per_probe), "allocating the ray set");
     SDF_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking), "creating a stream");
     SDF_TRY(hipEventCreateWithFlags(&c->ev_primary, hipEventDisableTiming), "creating events");
     SDF_TRY(hipEventCreateWithFlags(&c->ev_tail, hipEventDisableTiming), "creating events");
@@ -1054,7 +1050,7 @@ static sdfddgi_status create_ctx(const sdfddgi_sdf_grid *sdf, const HostClusters
         SDF_TRY(dev_alloc(&c->records, (size_t)P * c->main.R * 8), "allocating ray records");
     if (params->learned_rays > 0) {
         for (int k = 0; k < 2; ++k) {
-            SDF_TRY(alloc_set(c, c->low[k], params->learned_rays, true),
+            SDF_TRY(alloc_set(c, c->low[k], params->learned_rays),
                     "allocating the learned ray sets");
             SDF_TRY(alloc_set(c, c->fbs[k], params->rays_per_probe, true),
                     "allocating the learned ray sets");
@@ -1152,7 +1148,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     // right after the trace, only the lookups behind the previous frame's blend
     // (16384 x 256, ms per frame, FP32 / FP16: 0.7275 / 0.590 unsplit, 0.719 /
     // 0.576 split; that half's grid halved 0.736, not overlapped 0.734 in FP32)
-    const bool split = !serial && r.geo != nullptr;
+    const bool split = !serial && !c->analytic;
     // side stream: tables and primary trace. This set was last used by the frame
     // before the previous one, whose hit shading and blend ran before that set's
     // done event; so wait for that (the trace then starts as soon as its set is
@@ -1193,14 +1189,11 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
         // side2, after the weight rows: the atlas-independent half of the hit
         // shading; then the caller's stream, after the previous frame's blend: the
         // lookups into its atlas
-        TraceArgs tg = t;
-        tg.geo = r.geo;
         TRY_HIP(c, hipStreamWaitEvent(c->side2, c->ev_primary, 0), "stream wait");
         TRY_HIP(c, ev.mark_on(3, c->side2), "event");
-        TRY_HIP(c, launch_hits(tg, g, c->side2), "launching hits_kernel");
+        TRY_HIP(c, launch_hits(t, g, c->side2), "launching hits_kernel");
         TRY_HIP(c, hipEventRecord(r.ready, c->side2), "event");
         TRY_HIP(c, hipStreamWaitEvent(c->stream, r.ready, 0), "stream wait");
-        TRY_HIP(c, launch_shade(tg, c->stream), "launching shade_kernel");
     } else {
         // caller's stream: hit shading (reads the previous atlas, so after the
         // previous frame's blend)
@@ -1208,6 +1201,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
         TRY_HIP(c, ev.mark(3), "event");
         TRY_HIP(c, launch_hits(t, g, c->stream), "launching hits_kernel");
     }
+    TRY_HIP(c, launch_shade(t, c->stream), "launching shade_kernel");
     TRY_HIP(c, ev.mark(4), "event");
     TRY_HIP(c, launch_blend(blend_args(c, r, r.payload, c->prm.hysteresis, c->irr[c->cur],
                                        c->depth[c->cur], c->irr[nxt], c->depth[nxt], c->reject,
@@ -1552,7 +1546,6 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     // its hit shading
     TraceArgs tl = trace_pass(base, lo, lo.counter, lo.counter + kPartStride, nullptr, nullptr,
                               nullptr);
-    tl.geo = lo.geo;
     TRY_HIP(c, ev.mark_on(0, sl), "event");
     // only the directions block (it also resets the counters) ahead of the low
     // trace; the weight rows, which only the low-ray blend reads, on the caller's
@@ -1583,7 +1576,6 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     int *fb_count = fb.counter + 6;
     TraceArgs tf = trace_pass(base, fb, fb.counter, fb.counter + kPartStride, fb.list, fb_count,
                               nullptr);
-    tf.geo = fb.geo;
     TraceGrid gf = fb.grid;
     gf.primary_blocks = std::max(1, gf.primary_blocks_overlapped / 4);
     gf.hits_blocks = std::max(1, gf.hits_blocks_overlapped / 2);
@@ -1699,6 +1691,7 @@ sdfddgi_status sdfddgi_learned_examples(sdfddgi_ctx *c, const sdfddgi_denoiser *
                                     nullptr, nullptr);
     TRY_HIP(c, launch_primary(tl, lo.grid, c->stream), "launching primary_kernel");
     TRY_HIP(c, launch_hits(tl, lo.grid, c->stream), "launching hits_kernel");
+    TRY_HIP(c, launch_shade(tl, c->stream), "launching shade_kernel");
     TRY_HIP(c, launch_blend(blend_args(c, lo, lo.payload, 0.0f, c->irr[c->cur],
                                        c->depth[c->cur], c->u_irr, c->u_depth, nullptr, nullptr,
                                        nullptr),
@@ -2054,9 +2047,9 @@ struct sdfddgi_batch {
     char *cells = nullptr;                   // cell bricks of every scene's grid
     bool wide = false;                       // brick indices need 32-bit products
     float *alb[kMaxBatchScenes]{};
-    // Frames are pipelined like the single-scene ones: the tables and primary trace
-    // of frame f (the front graph, on the side stream) run beside frame f-1's hit
-    // shading and blend (the back graph, on the caller's stream). Everything a
+    // Frames are pipelined like the single-scene ones: the tables, the primary trace and
+    // the first half of the hit shading of frame f (the front graph, on the side stream)
+    // run beside frame f-1's lookups and blend (the back graph, on the caller's stream). Everything a
     // frame writes before its blend comes in two lanes; frame f uses lane f mod 2,
     // the same parity as the map pair it reads (cur).
     BatchScene *dev_scenes[2]{};              // per lane: the lane's table pointers
@@ -2068,6 +2061,7 @@ struct sdfddgi_batch {
     uint8_t *reject = nullptr;
     float4 *payload[2]{};
     int4 *hitq[2]{};
+    float4 *geo[2]{};
     int *counter[2]{};
     unsigned long long *stamps[2]{};         // [1 + S] per lane
     int last_lane = 0;                       // lane of the last frame
@@ -2116,7 +2110,7 @@ void batch_free(sdfddgi_batch *b) {
     }
     for (int k = 0; k < 2; ++k) {
         dev_free(b->dev_scenes[k]); dev_free(b->dirs[k]); dev_free(b->payload[k]);
-        dev_free(b->hitq[k]); dev_free(b->counter[k]); dev_free(b->stamps[k]);
+        dev_free(b->hitq[k]); dev_free(b->geo[k]); dev_free(b->counter[k]); dev_free(b->stamps[k]);
         dev_free(b->frame_dev[k]);
     }
     dev_free(b->probe_pos); dev_free(b->probe_order);
@@ -2149,6 +2143,7 @@ BatchArgs batch_args(const sdfddgi_batch *b, int cur, int lane) {
     a.prev_irr = b->irr[cur];
     a.payload = b->payload[lane];
     a.hitq = b->hitq[lane];
+    a.geo = b->geo[lane];
     a.counter = b->counter[lane];
     a.refill = b->tuning.refill;
     return a;
@@ -2156,9 +2151,10 @@ BatchArgs batch_args(const sdfddgi_batch *b, int cur, int lane) {
 
 // The launches of one frame reading map pair `cur` and writing the other, with
 // lane `lane`'s buffers (a frame normally uses lane cur), in two parts: the front
-// (counters, tables, primary trace; reads no map) and the back (hit shading, blend).
-// `ev` (may be null) receives events before the primary trace (front), and after
-// it, after the hit shading and (when ev[3] is set) after the blend (back).
+// (counters, tables, primary trace and the first half of the hit shading; reads no map)
+// and the back (lookups, blend). `ev` (may be null) receives events before and after the
+// primary trace and after the hit shading (front), and (when ev[3] is set) after the
+// blend (back).
 hipError_t batch_enqueue_front(sdfddgi_batch *b, int lane, const BatchTuning &t, hipStream_t st,
                                hipEvent_t *ev) {
     const int cur = lane;
@@ -2188,17 +2184,16 @@ hipError_t batch_enqueue_front(sdfddgi_batch *b, int lane, const BatchTuning &t,
     BatchArgs a = batch_args(b, cur, lane);
     a.refill = t.refill;
     if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
-    return launch_batch_primary(a, t, st);
+    if ((e = launch_batch_primary(a, t, st)) != hipSuccess) return e;
+    if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
+    if ((e = launch_batch_hits(a, t, st)) != hipSuccess) return e;
+    return ev ? hipEventRecord(ev[2], st) : hipSuccess;
 }
 
 hipError_t batch_enqueue_back(sdfddgi_batch *b, int cur, int lane, const BatchTuning &t,
                               hipStream_t st, hipEvent_t *ev) {
-    hipError_t e = hipSuccess;
-    BatchArgs a = batch_args(b, cur, lane);
-    a.refill = t.refill;
-    if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
-    if ((e = launch_batch_hits(a, t, st)) != hipSuccess) return e;
-    if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
+    hipError_t e = launch_batch_shade(batch_args(b, cur, lane), st);
+    if (e != hipSuccess) return e;
     BatchBlendArgs bb{};
     bb.nscenes = b->S;
     bb.scenes = b->dev_scenes[lane];
@@ -2540,6 +2535,7 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
     for (int k = 0; k < 2; ++k) {
         B_TRY(dev_alloc(&b->payload[k], (size_t)rays), "allocating payload");
         B_TRY(dev_alloc(&b->hitq[k], (size_t)rays), "allocating the hit queue");
+        B_TRY(dev_alloc(&b->geo[k], 2 * (size_t)rays), "allocating the hit records");
         B_TRY(dev_alloc(&b->counter[k], kBatchCounters), "allocating counters");
         B_TRY(dev_alloc(&b->stamps[k], 1 + (size_t)count), "allocating stamps");
         B_TRY(dev_alloc(&b->frame_dev[k], b->frame_bytes), "allocating frame constants");
@@ -2554,9 +2550,9 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
         B_TRY(hipEventCreateWithFlags(&b->frame_ev[k], hipEventDisableTiming), "creating events");
     }
     b->tuning.primary_chunk = 256;
-    b->tuning.primary_blocks = batch_max_blocks(dev, false);
+    b->tuning.primary_blocks = batch_resident_blocks(dev, false);
     b->tuning.hits_chunk = 64;
-    b->tuning.hits_blocks = batch_max_blocks(dev, true);
+    b->tuning.hits_blocks = batch_resident_blocks(dev, true);
     b->tuning.refill = 40;
     b->tuning.blend_probes = 16;
     b->tuning.blend_chunk = 64;
@@ -2659,7 +2655,8 @@ sdfddgi_status sdfddgi_batch_autotune(sdfddgi_batch *b, const sdfddgi_light *lig
     e = hipMemcpyAsync(saved, b->reject, (size_t)b->GP, hipMemcpyDeviceToDevice, b->stream);
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     for (int k = 0; k < 4 && e == hipSuccess; ++k) e = hipEventCreate(&ev[k]);
-    const int pmax = batch_max_blocks(b->device, false), hmax = batch_max_blocks(b->device, true);
+    const int pmax = batch_resident_blocks(b->device, false);
+    const int hmax = batch_resident_blocks(b->device, true);
     int count = 0;
     // time one configuration: mean primary, hit shading and blend kernel times over
     // `frames`

@@ -234,19 +234,19 @@ __device__ __forceinline__ int pack_hit(int kind, int level, int steps) {
 
 // Wave-level work feeder: claims `chunk` consecutive items per atomic and hands them
 // to idle lanes in order. All members are wave-uniform.
-template <int kChunkSize>
 struct Feeder {
-    int next = 0, end = 0;
+    int next = 0, end = 0, chunk;
     bool exhausted = false;
+    __device__ __forceinline__ explicit Feeder(int chunk_items) : chunk(chunk_items) {}
     // Returns the number of items given out; the rank-th idle lane takes first + rank.
     __device__ __forceinline__ int claim(int *counter, int total, int want, int &first) {
         if (next >= end) {
             int base = 0;
-            if (__lane_id() == 0) base = atomicAdd(counter, kChunkSize);
+            if (__lane_id() == 0) base = atomicAdd(counter, chunk);
             base = __builtin_amdgcn_readfirstlane(base);
             if (base >= total) { exhausted = true; return 0; }
             next = base;
-            end = min(base + kChunkSize, total);
+            end = min(base + chunk, total);
         }
         const int n = min(want, end - next);
         first = next;
@@ -254,6 +254,12 @@ struct Feeder {
         return n;
     }
 };
+
+// Whether the calling lane is in a wave-uniform mask.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// A ray waiting in LDS to be traced.
+struct WaitingRay { float4 from, dir; };
 
 // The XCD (accelerator complex die) the calling wave runs on, from the hardware
 // register that holds it; each XCD has its own L2.
