@@ -58,11 +58,42 @@ constexpr int kMaxClusters = 256;
 struct AnalyticArgs {
     int nprims, nclusters;
     const int *kind;                 // [nprims], primitives ordered by cluster
-    const int *orig;                 // [nprims] each one's index in the caller's order
-                                     //     (null: the cluster order is the caller's)
     const float *center, *half;      // [nprims][3] binary32
     const float *lo, *hi;            // [nclusters][3] widened bounding boxes
     const int *first;                // [nclusters + 1] first primitive of each cluster
+};
+
+// A primitive as the trace kernels hold it in LDS: (centre, a sphere's radius or 0) and
+// (half extents, 0 for a sphere; its index in the caller's order << 1 | kind).
+struct AnalyticPrim {
+    float4 c, h;
+};
+
+// The primitives of an analytic context and which of them can be the nearest, by levels
+// of cubic cells about `mid` with kCellPrims candidates each (analytic_common.h). Level 0
+// covers the primitives' box; level l, of cells 2^l times as wide, that box and
+// kCellMargin of its cells around it.
+constexpr int kCellPrims = 16;
+constexpr int kMaxCellLevels = 16;
+constexpr int kCellMargin = 8;
+// Cells of level 0, about. At 400 primitives and 16384 x 64 rays a frame takes 505, 523, 510,
+// 477, 530, 530 us with 2^14 .. 2^19: fewer candidates a cell against more lines. Listing them
+// takes 1.2 ms of the context's creation with 2^16 and 2.0 with 2^18.
+constexpr int kCandidateCells = 1 << 17;
+struct AnalyticScene {
+    const AnalyticPrim *prims;       // [nprims], ordered by cluster
+    int nprims, nclusters;
+    const float *lo, *hi;            // [nclusters][3] widened bounding boxes
+    const int *first;                // [nclusters + 1] first primitive of each cluster
+    const uint16_t *cells;           // [2][ncells][kCellPrims / 2] candidates
+    int nlevels, ncells;
+    float mid0, mid1, mid2, cell;    // centre of every level, side of level 0's cells
+    float inv;                       // (float)(1 / cell)
+    float half0, half1, half2;       // half level 0's box, in its cells
+    float beyond;                    // the last level's margin, in level 0's cells
+    float reach;                     // largest coordinate of a primitive's corner
+    float4 lv[kMaxCellLevels];       // half a level's cells along each axis (one cell of
+                                     //     rounding included), bits of its first cell's index
 };
 
 struct TraceArgs {
@@ -102,7 +133,7 @@ struct TraceArgs {
                                 //     level or -1 outside every level; analytic: the nearest
                                 //     primitive's slot); null: sample it
     int analytic;               // 1: distances from the primitives in `an`, not the grid
-    AnalyticArgs an;
+    AnalyticScene an;
     const float *prim_alb;      // [nprims][3] albedo of each primitive, cluster order
     float4 *geo;                // [P*R][2]: hits_kernel stores, per hit-queue entry i, what does
                                 //     not depend on the previous atlas -- geo[2i] = (normal, sun
@@ -169,7 +200,7 @@ hipError_t launch_tables(const TableArgs &a, hipStream_t stream);
 // alone; together they do what launch_tables does.
 hipError_t launch_tables_dirs(TableArgs a, hipStream_t stream);
 hipError_t launch_tables_weights(TableArgs a, hipStream_t stream);
-TraceGrid trace_grid(int device, int64_t rays, bool half, bool analytic = false);
+TraceGrid trace_grid(int device, int64_t rays, bool half, int analytic_prims = 0);
 hipError_t launch_primary(const TraceArgs &a, const TraceGrid &grid, hipStream_t stream);
 hipError_t launch_hits(const TraceArgs &a, const TraceGrid &grid, hipStream_t stream);
 // The atlas-dependent half of hit shading (TraceArgs::geo): one thread per queue entry.
@@ -411,6 +442,7 @@ struct AnalyticTrace {
     unsigned long long *evals;       // primitive distance evaluations (may be null)
 };
 
+hipError_t launch_candidate_cells(const AnalyticScene &a, uint16_t *cells, hipStream_t s);
 hipError_t launch_cluster_query(const AnalyticArgs &a, const float *pts, int n, int mode,
                                 float *out, unsigned long long *evals, hipStream_t stream);
 hipError_t launch_cluster_trace(const AnalyticArgs &a, const AnalyticTrace &r,

@@ -63,15 +63,16 @@ __device__ __forceinline__ int select_level(const TraceArgs &a, float x0, float 
 }
 
 // Distance backends of the trace kernels: the cascade of grids with binary32 or
-// binary16 values, or the scene's analytic primitives (Sec. 3.1) through the
-// cluster-culled query of Sec. 3.3. The per-workgroup LDS state of each:
+// binary16 values, or the scene's analytic primitives (Sec. 3.1) through their candidate
+// cells, which answer the cluster-culled query of Sec. 3.3. The per-workgroup LDS state of
+// each:
 enum : int { kSdfGrid32 = 0, kSdfGrid16 = 1, kSdfAnalytic = 2 };
 template <int kSdf> struct SdfLds { LevelLds lv[kMaxLevels]; };
-template <> struct SdfLds<kSdfAnalytic> { ClusterLds cl; };
+template <> struct SdfLds<kSdfAnalytic> { float4 lv[kMaxCellLevels]; };  // and lds_prims()
 
 template <int kSdf>
 __device__ __forceinline__ void load_sdf(const TraceArgs &a, SdfLds<kSdf> &s) {
-    if constexpr (kSdf == kSdfAnalytic) load_clusters(a.an, s.cl);
+    if constexpr (kSdf == kSdfAnalytic) load_prims(a.an, s.lv);
     else load_levels(a, s.lv);
 }
 
@@ -98,7 +99,7 @@ __device__ __forceinline__ GlobalBytes kept_cells(const TraceArgs &a) {
 // ray stops they stay, and stop_kind names the outcome from them, the sample's distance
 // and its level (-1 outside every level). Other lanes' values stay as they are.
 // Analytic backend: no grid box, so a ray misses only past t_max; the distance is
-// the culled minimum over the primitives, starting from `bound` (the previous
+// the minimum over the cell's primitives, starting from `bound` (the previous
 // sample's bound, +inf at a ray's first sample), and a primary ray's sample names
 // its nearest primitive in `slot` (level is 0).
 template <bool kPrimary, int kSdf, bool kWide>
@@ -111,14 +112,8 @@ __device__ __forceinline__ uint64_t trace_step(const TraceArgs &a, GlobalBytes c
     uint64_t inside = live & ~__ballot(t > a.t_max);
     if constexpr (kSdf == kSdfAnalytic) {
         level = 0;
-        if (in_mask(inside)) {
-            if (kPrimary) {
-                dist = nearest_distance(a.an, s.cl, x0, x1, x2, bound, slot);
-            } else {
-                uint32_t evals = 0;
-                dist = scene_distance(a.an, s.cl, 2, x0, x1, x2, bound, evals);
-            }
-        }
+        if (in_mask(inside))
+            dist = analytic_distance<kPrimary>(a.an, s.lv, x0, x1, x2, bound, slot);
     } else {
         constexpr bool kHalf = kSdf == kSdfGrid16;
         const int found = select_level(a, x0, x1, x2);
@@ -234,7 +229,6 @@ constexpr int kHitChunk = 64;     // queued hits claimed at a time (spreads them
 constexpr int kXcdBlockRays = 65536;
 constexpr int kEndBatch = 16;     // idle lanes at which a wave records ended rays and goes on
 constexpr int kFetchAt = 48;      // a wave fetches 64 more rays when no more than these wait
-constexpr int kAnalyticBin = 64;  // probes whose rays of one direction the analytic trace groups
 
 // Primary sphere trace, persistent and wave-compacted: each lane owns one ray and takes
 // one sample per iteration. Once kEndBatch lanes are idle the wave records the rays that
@@ -258,9 +252,7 @@ template <int kSdf, bool kWide = false>
 __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
     __shared__ SdfLds<kSdf> s_sdf;
     __shared__ int4 s_hits[4][64];
-    // the primitives' LDS leaves room for the fetch in hand only
-    constexpr int kRayQueue = kSdf == kSdfAnalytic ? 64 : 128;
-    constexpr int kQueueAhead = kSdf == kSdfAnalytic ? 0 : kFetchAt;
+    constexpr int kRayQueue = 128;
     // origin and the distance of the first sample (0: not taken), direction and index
     __shared__ WaitingRay s_rays[4][kRayQueue];
     load_sdf<kSdf>(a, s_sdf);
@@ -366,7 +358,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
                 waiting -= n;
             }
             if (stage == 0 && !feed.exhausted &&
-                (plenty ? waiting <= kQueueAhead : __popcll(live) <= 32)) {
+                (plenty ? waiting <= kFetchAt : __popcll(live) <= 32)) {
                 RareArgs &f = *rare_args();
                 coming = 0;
                 while (coming < 64 && !feed.exhausted) {
@@ -376,23 +368,10 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
                         // slot -> (probe in Morton order, ray): neighbouring slots trace
                         // neighbouring probes, so the rays in flight share cache lines
                         const int sid = first + lane - coming;
-                        int q, i;
-                        if constexpr (kSdf == kSdfAnalytic) {
-                            // groups of kAnalyticBin probes of the Morton order, consecutive
-                            // slots taking one direction across the group's probes: a wave's
-                            // lanes march side by side from neighbouring probes, so the
-                            // clusters that any lane's bound admits stay few
-                            const int nq = total / f.R, gsz = kAnalyticBin * f.R;
-                            const int g = sid / gsz, within = sid - g * gsz;
-                            const int gq = min(kAnalyticBin, nq - g * kAnalyticBin);
-                            i = within / gq;
-                            q = g * kAnalyticBin + (within - i * gq);
-                        } else {
-                            // sid / R: at most one too large (sid < 2^31, R <= 2^10)
-                            q = (int)__umulhi((uint32_t)sid, f.r_magic);
-                            i = sid - q * f.R;
-                            if (i < 0) { --q; i += f.R; }
-                        }
+                        // sid / R: at most one too large (sid < 2^31, R <= 2^10)
+                        int q = (int)__umulhi((uint32_t)sid, f.r_magic);
+                        int i = sid - q * f.R;
+                        if (i < 0) { --q; i += f.R; }
                         n_probe = f.probe_order[q];
                         v0 = f.dirs[3 * i]; v1 = f.dirs[3 * i + 1]; v2 = f.dirs[3 * i + 2];
                         n_ray = i;
@@ -459,7 +438,7 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
                 float n0, n1, n2;
                 float3 alb;
                 if constexpr (kSdf == kSdfAnalytic) {
-                    analytic_normal(s_sdf.cl, e.w, x0, x1, x2, w0, w1, w2, n0, n1, n2);
+                    analytic_normal(e.w, x0, x1, x2, w0, w1, w2, n0, n1, n2);
                     alb = make_float3(f.prim_alb[3 * e.w], f.prim_alb[3 * e.w + 1],
                                       f.prim_alb[3 * e.w + 2]);
                 } else {
@@ -869,13 +848,13 @@ __global__ __launch_bounds__(256) void probe_first_kernel(TraceArgs a, int2 *out
 // The same for the analytic backend: the culled query's distance at the probe from an
 // unbounded start, and the nearest primitive's slot.
 __global__ __launch_bounds__(256) void probe_first_analytic_kernel(TraceArgs a, int2 *out) {
-    __shared__ ClusterLds s_cl;
-    load_clusters(a.an, s_cl);
+    __shared__ float4 s_lv[kMaxCellLevels];
+    load_prims(a.an, s_lv);
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.P) return;
-    int slot = -1;
-    const float d = nearest_distance(a.an, s_cl, a.probe_pos[3 * p], a.probe_pos[3 * p + 1],
-                                     a.probe_pos[3 * p + 2], INFINITY, slot);
+    int slot;
+    const float d = analytic_distance<true>(a.an, s_lv, a.probe_pos[3 * p], a.probe_pos[3 * p + 1],
+                                            a.probe_pos[3 * p + 2], INFINITY, slot);
     out[p] = make_int2(__float_as_int(d), slot);
 }
 
@@ -983,9 +962,10 @@ hipError_t launch_tables_weights(TableArgs a, hipStream_t s) {
 // Persistent grids: as many 256-thread blocks as fit on the device at once, at most
 // max_per_cu per compute unit (fewer when there are fewer rays). A block is one wave
 // per SIMD.
-static int persistent_blocks(const void *kernel, int device, int64_t rays, int max_per_cu) {
+static int persistent_blocks(const void *kernel, int device, int64_t rays, int max_per_cu,
+                             size_t lds) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, lds) != hipSuccess)
         per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         cus = 1;
@@ -1008,19 +988,21 @@ constexpr int kPrimaryBlocksPerCuOverlapped[2] = {3, 4};  // binary32, binary16 
 constexpr int kHitsBlocksPerCu = 2;
 constexpr int kHitsBlocksPerCuOverlapped = 1;
 
-TraceGrid trace_grid(int device, int64_t rays, bool half, bool analytic) {
+TraceGrid trace_grid(int device, int64_t rays, bool half, int analytic_prims) {
     TraceGrid g;
+    const bool analytic = analytic_prims > 0;
+    const size_t lds = analytic_prims * sizeof(AnalyticPrim);
     const void *pk = analytic ? (const void *)primary_kernel<kSdfAnalytic>
                      : half   ? (const void *)primary_kernel<kSdfGrid16>
                               : (const void *)primary_kernel<kSdfGrid32>;
-    g.primary_blocks = persistent_blocks(pk, device, rays, kPrimaryBlocksPerCu);
+    g.primary_blocks = persistent_blocks(pk, device, rays, kPrimaryBlocksPerCu, lds);
     g.primary_blocks_overlapped =
-        persistent_blocks(pk, device, rays, kPrimaryBlocksPerCuOverlapped[half ? 1 : 0]);
+        persistent_blocks(pk, device, rays, kPrimaryBlocksPerCuOverlapped[half ? 1 : 0], lds);
     const void *hk = analytic ? (const void *)hits_kernel<kSdfAnalytic>
                      : half   ? (const void *)hits_kernel<kSdfGrid16>
                               : (const void *)hits_kernel<kSdfGrid32>;
-    g.hits_blocks = persistent_blocks(hk, device, rays, kHitsBlocksPerCu);
-    g.hits_blocks_overlapped = persistent_blocks(hk, device, rays, kHitsBlocksPerCuOverlapped);
+    g.hits_blocks = persistent_blocks(hk, device, rays, kHitsBlocksPerCu, lds);
+    g.hits_blocks_overlapped = persistent_blocks(hk, device, rays, kHitsBlocksPerCuOverlapped, lds);
     return g;
 }
 
@@ -1028,7 +1010,8 @@ TraceGrid trace_grid(int device, int64_t rays, bool half, bool analytic) {
 #define SDFDDGI_LAUNCH_TRACE(kernel, blocks)                                                       \
     do {                                                                                           \
         if (a.analytic)                                                                            \
-            hipLaunchKernelGGL(kernel<kSdfAnalytic>, dim3(blocks), dim3(256), 0, s, a);            \
+            hipLaunchKernelGGL(kernel<kSdfAnalytic>, dim3(blocks), dim3(256),                      \
+                               a.an.nprims * sizeof(AnalyticPrim), s, a);                          \
         else if (a.half_sdf && a.wide)                                                             \
             hipLaunchKernelGGL(HIP_KERNEL_NAME(kernel<kSdfGrid16, true>), dim3(blocks), dim3(256), \
                                0, s, a);                                                           \
@@ -1096,8 +1079,8 @@ hipError_t launch_probe_sdf(const TraceArgs &a, float *out, hipStream_t s) {
 
 hipError_t launch_probe_first(const TraceArgs &a, int2 *out, hipStream_t s) {
     if (a.analytic)
-        hipLaunchKernelGGL(probe_first_analytic_kernel, dim3(blocks_for(a.P, 256)), dim3(256), 0,
-                           s, a, out);
+        hipLaunchKernelGGL(probe_first_analytic_kernel, dim3(blocks_for(a.P, 256)), dim3(256),
+                           a.an.nprims * sizeof(AnalyticPrim), s, a, out);
     else if (a.half_sdf)
         hipLaunchKernelGGL(probe_first_kernel<true>, dim3(blocks_for(a.P, 256)), dim3(256), 0, s, a,
                            out);

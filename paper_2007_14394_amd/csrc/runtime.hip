@@ -217,10 +217,11 @@ struct sdfddgi_ctx {
     float *mean_error = nullptr;                     // [P]
     // analytic scene (sdfddgi_create_analytic): the primitives in cluster order
     bool analytic = false;
-    int an_nprims = 0, an_nclusters = 0;
-    int *an_kind = nullptr, *an_orig = nullptr, *an_first = nullptr;
-    float *an_center = nullptr, *an_half = nullptr, *an_lo = nullptr, *an_hi = nullptr;
-    float *an_alb = nullptr;
+    AnalyticScene an{};                              // its pointers: the an_ buffers below
+    AnalyticPrim *an_prims = nullptr;
+    int *an_first = nullptr;
+    float *an_lo = nullptr, *an_hi = nullptr, *an_alb = nullptr;
+    uint16_t *an_cells = nullptr;
     // Timing: kEvents events per frame in a ring (see sdfddgi_get_kernel_times);
     // sdfddgi_get_kernel_times averages the frames recorded since its previous call.
     hipEvent_t *ev_ring = nullptr;
@@ -335,8 +336,8 @@ void free_all(sdfddgi_ctx *c) {
     dev_free(c->u_irr); dev_free(c->u_depth);
     dev_free(c->probe_sdf); dev_free(c->texel_dir); dev_free(c->mean_error);
     dev_free(c->fb_flag[0]); dev_free(c->fb_flag[1]);
-    dev_free(c->an_kind); dev_free(c->an_orig); dev_free(c->an_first); dev_free(c->an_center);
-    dev_free(c->an_half); dev_free(c->an_lo); dev_free(c->an_hi); dev_free(c->an_alb);
+    dev_free(c->an_prims); dev_free(c->an_first); dev_free(c->an_cells);
+    dev_free(c->an_lo); dev_free(c->an_hi); dev_free(c->an_alb);
     if (c->ev_ring) {
         for (int k = 0; k < kEvents * kTimingRing; ++k)
             if (c->ev_ring[k]) (void)hipEventDestroy(c->ev_ring[k]);
@@ -518,6 +519,65 @@ std::string build_clusters(int nprims, const int32_t *kind, const double *center
     return std::string();
 }
 
+// The candidate cells' levels: about kCandidateCells cubic cells over the primitives'
+// bounding box (no axis shorter than 1/16 of the longest), then margins of twice the width
+// each until they hold every point that a ray of the probes can sample. What lies beyond,
+// and a scene whose coordinates overflow, walks the clusters.
+AnalyticScene candidate_levels(const HostClusters &h, const sdfddgi_probe_grid &pg,
+                               const sdfddgi_params &prm) {
+    AnalyticScene a{};
+    a.nprims = h.nprims;
+    a.nclusters = h.nclusters;
+    double ext[3], mid[3], reach = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int k = 0; k < h.nclusters; ++k) {
+            lo = std::min(lo, (double)h.lo[3 * (size_t)k + c]);
+            hi = std::max(hi, (double)h.hi[3 * (size_t)k + c]);
+        }
+        mid[c] = 0.5 * (lo + hi);
+        ext[c] = hi - lo;   // above 0: the clusters' boxes are widened
+        reach = std::max(reach, std::max(std::fabs(lo), std::fabs(hi)));
+    }
+    if (!(reach < 1e18)) {   // binary32 distances overflow: each cell lists all, or walks
+        reach = INFINITY;
+        for (int c = 0; c < 3; ++c) { mid[c] = 0.0; ext[c] = 1.0; }
+    }
+    const double longest = std::max(ext[0], std::max(ext[1], ext[2]));
+    double volume = 1.0;
+    for (double &e : ext) volume *= e = std::max(e, longest / 16.0);
+    const double cell = std::cbrt(volume / kCandidateCells);
+    int half[3];
+    double out = 0.0;   // how far a ray can get beyond level 0's box, in its cells
+    for (int c = 0; c < 3; ++c) {
+        half[c] = (int)std::ceil(0.5 * ext[c] / cell);
+        for (int e = 0; e < 2; ++e) {
+            const double x = pg.origin[c] + e * pg.spacing[c] * (pg.n[c] - 1);
+            out = std::max(out, (std::fabs(x - mid[c]) + prm.t_max) / cell - half[c]);
+        }
+    }
+    while (a.nlevels < kMaxCellLevels && (a.nlevels == 0 || !(out < a.beyond))) {
+        const int l = a.nlevels++, margin = l ? kCellMargin + 1 : 1;
+        float n[3];
+        int32_t cells = 1;
+        for (int c = 0; c < 3; ++c) {
+            const int k = ((half[c] - 1) >> l) + 1 + margin;
+            n[c] = (float)k;
+            cells *= 2 * k;
+        }
+        a.lv[l] = make_float4(n[0], n[1], n[2], 0.0f);
+        std::memcpy(&a.lv[l].w, &a.ncells, 4);
+        a.ncells += cells;
+        a.beyond = l ? std::ldexp((float)kCellMargin, l) : 0.0f;
+    }
+    a.mid0 = (float)mid[0]; a.mid1 = (float)mid[1]; a.mid2 = (float)mid[2];
+    a.cell = (float)cell;
+    a.inv = (float)(1.0 / cell);
+    a.half0 = (float)half[0]; a.half1 = (float)half[1]; a.half2 = (float)half[2];
+    a.reach = (float)reach;
+    return a;
+}
+
 // Monotone integer key of a binary32 value (orders all finite floats).
 int32_t float_key(float f) {
     int32_t b;
@@ -647,7 +707,7 @@ hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool listed = false) {
         chk(hipMemsetAsync(r.w16_i, 0, (size_t)c->Tpi * r.Rpad * 2, c->stream));
         chk(hipMemsetAsync(r.w16_d, 0, (size_t)c->Tpd * r.Rpad * 2, c->stream));
     }
-    r.grid = trace_grid(c->device, c->P * R, c->half, c->analytic);
+    r.grid = trace_grid(c->device, c->P * R, c->half, c->analytic ? c->an.nprims : 0);
     return e;
 }
 
@@ -739,15 +799,7 @@ TraceArgs trace_base(const sdfddgi_ctx *c, const float l[3], const float rad[3])
     t.prev_irr = c->irr[c->cur];
     if (c->analytic) {
         t.analytic = 1;
-        t.an.nprims = c->an_nprims;
-        t.an.nclusters = c->an_nclusters;
-        t.an.kind = c->an_kind;
-        t.an.orig = c->an_orig;
-        t.an.center = c->an_center;
-        t.an.half = c->an_half;
-        t.an.lo = c->an_lo;
-        t.an.hi = c->an_hi;
-        t.an.first = c->an_first;
+        t.an = c->an;
         t.prim_alb = c->an_alb;
     }
     return t;
@@ -940,33 +992,39 @@ static sdfddgi_status create_ctx(const sdfddgi_sdf_grid *sdf, const HostClusters
         }
     }
     if (hc) {
-        c->an_nprims = hc->nprims;
-        c->an_nclusters = hc->nclusters;
         const size_t n3 = 3 * (size_t)hc->nprims, k3 = 3 * (size_t)hc->nclusters;
-        SDF_TRY(dev_alloc(&c->an_kind, hc->nprims), "allocating primitives");
-        SDF_TRY(dev_alloc(&c->an_orig, hc->nprims), "allocating primitives");
+        std::vector<AnalyticPrim> prims((size_t)hc->nprims);
+        for (int j = 0; j < hc->nprims; ++j) {
+            const float *x = &hc->cen[3 * (size_t)j], *h = &hc->half[3 * (size_t)j];
+            const bool box = hc->kind[j] != 0;
+            const int32_t key = hc->orig[j] << 1 | hc->kind[j];
+            prims[j].c = make_float4(x[0], x[1], x[2], box ? 0.0f : h[0]);
+            prims[j].h = box ? make_float4(h[0], h[1], h[2], 0.0f) : make_float4(0, 0, 0, 0);
+            std::memcpy(&prims[j].h.w, &key, 4);
+        }
+        c->an = candidate_levels(*hc, *probes, *params);
+        SDF_TRY(dev_alloc(&c->an_prims, hc->nprims), "allocating primitives");
+        SDF_TRY(dev_alloc(&c->an_cells, (size_t)c->an.ncells * kCellPrims), "allocating primitives");
         SDF_TRY(dev_alloc(&c->an_first, hc->nclusters + 1), "allocating primitives");
-        SDF_TRY(dev_alloc(&c->an_center, n3), "allocating primitives");
-        SDF_TRY(dev_alloc(&c->an_half, n3), "allocating primitives");
         SDF_TRY(dev_alloc(&c->an_alb, n3), "allocating primitives");
         SDF_TRY(dev_alloc(&c->an_lo, k3), "allocating primitives");
         SDF_TRY(dev_alloc(&c->an_hi, k3), "allocating primitives");
-        SDF_TRY(hipMemcpy(c->an_kind, hc->kind.data(), hc->nprims * sizeof(int),
-                          hipMemcpyHostToDevice), "uploading primitives");
-        SDF_TRY(hipMemcpy(c->an_orig, hc->orig.data(), hc->nprims * sizeof(int),
+        SDF_TRY(hipMemcpy(c->an_prims, prims.data(), prims.size() * sizeof(AnalyticPrim),
                           hipMemcpyHostToDevice), "uploading primitives");
         SDF_TRY(hipMemcpy(c->an_first, hc->first.data(), (hc->nclusters + 1) * sizeof(int),
                           hipMemcpyHostToDevice), "uploading primitives");
-        SDF_TRY(hipMemcpy(c->an_center, hc->cen.data(), n3 * sizeof(float), hipMemcpyHostToDevice),
-                "uploading primitives");
-        SDF_TRY(hipMemcpy(c->an_half, hc->half.data(), n3 * sizeof(float), hipMemcpyHostToDevice),
-                "uploading primitives");
         SDF_TRY(hipMemcpy(c->an_alb, hc->alb.data(), n3 * sizeof(float), hipMemcpyHostToDevice),
                 "uploading primitives");
         SDF_TRY(hipMemcpy(c->an_lo, hc->lo.data(), k3 * sizeof(float), hipMemcpyHostToDevice),
                 "uploading primitives");
         SDF_TRY(hipMemcpy(c->an_hi, hc->hi.data(), k3 * sizeof(float), hipMemcpyHostToDevice),
                 "uploading primitives");
+        c->an.prims = c->an_prims;
+        c->an.first = c->an_first;
+        c->an.lo = c->an_lo;
+        c->an.hi = c->an_hi;
+        c->an.cells = c->an_cells;
+        SDF_TRY(launch_candidate_cells(c->an, c->an_cells, c->stream), "listing candidates");
     }
 
     // Host constants in binary64: probe positions (rounded once), the probes'

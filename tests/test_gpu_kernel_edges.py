@@ -2,7 +2,8 @@
 can go wrong: grids thinner and longer than a brick, ragged bricks, primitive counts
 around the staging chunk, equal and non-finite primitives; maps whose float counts are
 not multiples of four; grids at the edges of the trace's cell bricks, too long for its
-24-bit products, and levels that are not nested."""
+24-bit products, and levels that are not nested; analytic scenes whose candidate cells
+hold one to too many primitives, and rays beyond them."""
 import sys
 
 import numpy as np
@@ -144,3 +145,40 @@ def test_trace_covers_every_ray(S, probes, rays):
     announce(f"{probes} probes x {rays} rays")
     w = scenegen.small_cascade(3, probes=probes, rays=rays)
     check_trace(S, w, False)
+
+# Candidate cells of an analytic scene: lists of one, of up to 8 and up to 16 primitives,
+# cells of more (equal primitives; many at one centre), which walk the clusters, rays that
+# start and end beyond the outermost level, a plane of centres and one lone primitive.
+@pytest.mark.parametrize("count,kind", [(1, "lone"), (60, "open"), (24, "equal"), (40, "shells"),
+                                        (200, "flat"), (1024, "open")])
+@pytest.mark.parametrize("t_max,spread", [(9.0, 1.0), (4000.0, 90.0)])
+def test_analytic_candidate_cells(S, count, kind, t_max, spread):
+    announce(f"candidates {count} {kind} t_max {t_max} spread {spread}")
+    p = scenegen.open_scene_primitives(np.random.default_rng(count), count, (-4.0, 0.0, -4.0),
+                                       (4.0, 2.0, 4.0), size_range=(0.1, 0.5))
+    if kind == "equal":          # ties of every primitive: the lowest index is the nearest
+        for f in (p.kind, p.center, p.half):
+            f[:] = f[0]
+    elif kind == "shells":       # 40 spheres about one centre, and as far from a far point
+        p.kind[:] = 0
+        p.center[:] = (0.5, 1.0, -0.25)
+        p.half[:] = np.linspace(0.05, 0.6, count)[:, None]
+    elif kind == "flat":
+        p.center[:, 1] = 0.0
+    params = Params(rays_per_probe=48, t_max=t_max, sky_rgb=(0.3, 0.2, 0.1))
+    probes = ProbeGrid((4, 3, 4), (-1.7 * spread, 0.4, -1.6 * spread),
+                       (1.1 * spread, 0.7 * spread, 1.05 * spread))
+    w = Workload("candidates", p, [], probes, params, [])
+    rec = []
+    f = frame((0.3, 1.0, 0.2), seed=78)
+    for cluster in (8, 5):
+        ctx = S.context_from_workload(w, flags=S.SDFDDGI_FLAG_RECORD_RAYS, analytic=True,
+                                      cluster_size=cluster)
+        S.sdfddgi_update_frame(ctx, f.dir_to_light, f.radiance_rgb, f.rotation_seed)
+        rec.append(S.sdfddgi_get_ray_records(ctx).cpu().numpy())
+        S.sdfddgi_destroy(ctx)
+    irr0, dep0 = (np.zeros(s, np.float32) for s in scenegen.atlas_shapes(w.num_probes, params))
+    _, _, _, ref = oracle.Checker(w, analytic=True).update_probes(f, True, irr0, dep0,
+                                                                  want_records=True)
+    assert np.array_equal(rec[0], ref)
+    assert np.array_equal(rec[1], ref)
