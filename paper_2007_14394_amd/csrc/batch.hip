@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256) void batch_shade_kernel(BatchArgs a) {
 // 16-probe block table): that scene's blend arguments, the shared precision-form
 // blend body with the tile (kP, kChunk), then the scene's end stamp.
 template <int kP, int kChunk>
-__global__ __launch_bounds__(256) void batch_blend_kernel(BatchBlendArgs b) {
+__global__ __launch_bounds__(256, 4) void batch_blend_kernel(BatchBlendArgs b) {
     constexpr int kSub = kBlendProbes / kP;
     const int2 blk = b.blocks[blockIdx.x / kSub];
     const int pb = blk.y + (int)(blockIdx.x % kSub) * kP;
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(256) void batch_blend_kernel(BatchBlendArgs b) {
     a.new_irr = b.new_irr + ti;
     a.new_depth = b.new_depth + td;
     a.reject = b.reject + s.probe_base;
-    blend16_block<true, kP, kChunk>(a, pb);
+    blend16_block<kStdMaps, kP, kChunk>(a, pb);
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();

@@ -147,9 +147,20 @@ struct TraceGrid {
     int hits_blocks_overlapped = 0;     // hit shading beside the next frame's primary trace
 };
 
+// Where the weight of texel t and ray i stands in a table of Rpad rays: in the order in
+// which the blend's waves read their operands, kRays rays of 16 texels (16 in binary32, 32
+// in 16 bits: four products, or one) as 64 lanes of kRays / 4 values each, 1 KB side by
+// side. (With one row of rays per texel a wave's read took half a line of each of 16 rows,
+// all in the same few channels of the L2.)
+template <int kRays>
+__host__ __device__ __forceinline__ size_t weight_index(int t, int i, int Rpad) {
+    constexpr int kLane = kRays / 4;
+    return ((size_t)((t >> 4) * (Rpad / kRays) + i / kRays) * 64 + (i % kRays) / kLane * 16 + (t & 15)) *
+               kLane + i % kLane;
+}
+
 struct TableArgs {
     int R, Ti, Td;
-    int Tpi, Tpd;               // row strides of the weight tables: T rounded up to 16
     double q[9];                // frame rotation, row-major
     const double *q_dev;        // null: q above; else the rotation read from device memory
                                 //     (a captured graph replays with per-frame values)
@@ -158,15 +169,16 @@ struct TableArgs {
     const double *texel_i;      // [Ti][3] irradiance texel directions
     const double *texel_d;      // [Td][3] depth texel directions
     float *dirs;                // [R][3]
-    float *wt_i;                // [R][Tpi] w_ti, transposed; rows t >= Ti stay zero
-    float *wt_d;                // [R][Tpd] w_ti^s, transposed; rows t >= Td stay zero
+    float *wt_i;                // w_ti as the blend's operands (weight_index): Tp Rpad values,
+                                //     Tp = T rounded up to 16, the rest stays zero
+    float *wt_d;                // w_ti^s, likewise
     float *norm_i;              // [Ti]  pi / sum_i w_ti   (-1: all weights vanish)
     float *norm_d;              // [Td]  1 / sum_i w_ti^s  (-1: all weights vanish)
     int *counter;               // [ncounter] counters reset here (may be null): the trace
     int ncounter;               //     kernels' and, in the learned form, the fallback pass's
-    int Rpad;                   // row length of the 16-bit tables: R rounded up to 64
-    _Float16 *w16_i;            // precision form: [Tpi][Rpad] FP16 w_ti (else null)
-    __bf16 *w16_d;              // precision form: [Tpd][Rpad] BF16 w_ti^s (else null)
+    int Rpad;                   // R rounded up to 64
+    _Float16 *w16_i;            // precision form: FP16 w_ti, BF16 w_ti^s (else null)
+    __bf16 *w16_d;
     int row0;                   // row of block 0 (set by the launch functions)
 };
 

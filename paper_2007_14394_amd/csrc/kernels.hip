@@ -587,18 +587,18 @@ __global__ __launch_bounds__(256) void tables_kernel(TableArgs a) {
             w = pow(w, a.sharp);
             if (a.w16_d) {  // precision form: BF16 depth weights, sums of the rounded values
                 const __bf16 b = (__bf16)(float)w;
-                a.w16_d[(size_t)t * a.Rpad + i] = b;
+                a.w16_d[weight_index<32>(t, i, a.Rpad)] = b;
                 w = (double)(float)b;
             } else {
-                a.wt_d[(size_t)i * a.Tpd + t] = (float)w;
+                a.wt_d[weight_index<16>(t, i, a.Rpad)] = (float)w;
             }
         } else {
             if (a.w16_i) {  // precision form: FP16 irradiance weights
                 const _Float16 h = (_Float16)w;
-                a.w16_i[(size_t)t * a.Rpad + i] = h;
+                a.w16_i[weight_index<32>(t, i, a.Rpad)] = h;
                 w = (double)(float)h;
             } else {
-                a.wt_i[(size_t)i * a.Tpi + t] = (float)w;
+                a.wt_i[weight_index<16>(t, i, a.Rpad)] = (float)w;
             }
         }
         part += w;
@@ -622,166 +622,165 @@ __global__ __launch_bounds__(256) void tables_kernel(TableArgs a) {
     }
 }
 
-template <bool kStd>
-__global__ __launch_bounds__(256) void blend16_kernel(BlendArgs a) {
-    blend16_block<kStd>(a, blockIdx.x * kBlendProbes);
+template <int kMaps, int kP>
+__global__ __launch_bounds__(256, 4) void blend16_kernel(BlendArgs a) {
+    blend16_block<kMaps, kP>(a, blockIdx.x * kP);
 }
 
-// kStd: the 8x8 irradiance + 16x16 depth layout (4 + 16 M-tiles, one pass), where
-// slot 0 of every wave is an irradiance tile and slots 1..4 are depth tiles, known at
-// compile time; other resolutions take the general instantiation.
-template <bool kStd>
-__global__ __launch_bounds__(256) void blend_kernel(BlendArgs a) {
-    // payload of 16 probes x 4 channels x 64 rays, plus one zero row for absent
-    // probes; the standard layout's epilogue reuses the buffer
-    constexpr int kStage = (kBlendProbes * 4 + 1) * kBlendPitch;
-    __shared__ float sbuf[kStage > kEpilogueFloats ? kStage : kEpilogueFloats];
-    float *sx = sbuf;
-    __shared__ float s_h[kBlendProbes];
-    __shared__ int s_pid[kBlendProbes];
+// One workgroup's share (probe slots pb .. pb+kP-1) of the FP32 blend. Sixteen rays make
+// four products: lane group g takes rays 4 g .. 4 g + 3 of both operands, one ray per
+// product, so that a lane's operands for all four are 16 bytes side by side -- the
+// weights' in their table (a step's read while the one before is multiplied), the
+// payload's in its LDS column. The next 64 rays' payload is read while the present ones
+// are multiplied.
+// At 16384 x 256 and 8x8 + 16x16 maps: 81 us, of which 37.5 are the matrix cores' (they
+// reach 151 TFLOP/s of binary32 at best) and some 20 the reading and writing of the maps,
+// which the workgroups of a CU come to at about the same time. One dword per operand and
+// product from tables of one row per ray, and an epilogue through three passes over LDS:
+// 114 us. Raising the waves' priority by their slot, to pull the workgroups of a CU apart,
+// gave nothing.
+template <int kMaps, int kP>
+__device__ __forceinline__ void blend32_block(const BlendArgs &a, int pb) {
+    constexpr bool kStd = kMaps == kStdMaps;
+    constexpr int kIS = kStd ? kIrrSlots : kIrrSlotsAny, kSlots = kIS + kDepthSlots;
+    constexpr int kPitch = kBlendChunk + 4;   // a column's rays; +4 spreads the banks
+    constexpr int kNi = (3 * kP + 15) / 16, kNd = (2 * kP + 15) / 16;
+    // payload of kP probes x 4 channels, plus one zero column for absent probes; the
+    // epilogue through LDS reuses the buffer
+    constexpr int kStage = (kP * 4 + 1) * kPitch, kBuf = kP * (kStd ? kProbeFloatsStd : kProbeFloatsAny);
+    __shared__ __attribute__((aligned(16))) float sbuf[kStage > kBuf ? kStage : kBuf];
+    __shared__ float s_h[kP];
+    __shared__ int s_pid[kP];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, krow = lane >> 4;
-    const int pb = blockIdx.x * kBlendProbes;
     const int count = a.probe_list ? min(*a.probe_count, a.P) : a.P;
     if (pb >= count) return;
-    const int np = min(kBlendProbes, count - pb);
-    const int ri = a.irr_res, rd = a.depth_res;
-    const int Ti = ri * ri, Td = rd * rd;
+    const int np = min(kP, count - pb);
+    const int Ti = a.irr_res * a.irr_res, Td = a.depth_res * a.depth_res;
     const int mti = (Ti + 15) >> 4, mtd = (Td + 15) >> 4;
-    const int Tpi = mti * 16, Tpd = mtd * 16;   // padded rows of the weight tables
-    const int mtiles = mti + mtd;
-    const int si = ri + 2, sd = rd + 2;
-    constexpr int kZeroRow = kBlendProbes * 4 * kBlendPitch;
-    load_blend_probes(a, pb, np, s_pid, s_h);
-    for (int e = tid; e < kBlendPitch; e += 256) sx[kZeroRow + e] = 0.0f;
+    load_blend_probes<kP>(a, pb, np, s_pid, s_h);
+    for (int e = tid; e < kPitch; e += 256) sbuf[kP * 4 * kPitch + e] = 0.0f;
 
-    // B-operand columns of this lane: irradiance (q, c) for 3 N-tiles, depth (q, m) for 2
-    int bi_off[3], bd_off[2];
-    bool bd_sq[2];
+    // B-operand columns of this lane: irradiance (q, c), depth (q, m)
+    int bi_off[kNi], bd_off[kNd];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) {
-        const int col = n * 16 + row, q = col / 3, c = col - 3 * (col / 3);
-        bi_off[n] = q < np ? (q * 4 + c) * kBlendPitch : kZeroRow;
+    for (int n = 0; n < kNi; ++n) {
+        const int col = n * 16 + row, q = col / 3, c = col - 3 * q;
+        bi_off[n] = (q < np ? q * 4 + c : kP * 4) * kPitch + 4 * krow;
     }
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-        const int col = n * 16 + row, q = col >> 1;
-        bd_off[n] = q < np ? (q * 4 + 3) * kBlendPitch : kZeroRow;
-        bd_sq[n] = (col & 1) != 0;
+    for (int n = 0; n < kNd; ++n) {
+        const int q = (n * 16 + row) >> 1;
+        bd_off[n] = (q < np ? q * 4 + 3 : kP * 4) * kPitch + 4 * krow;
     }
+    const bool square = (row & 1) != 0;
 
-    const int passes = kStd ? 1 : (mtiles + 4 * kMSlots - 1) / (4 * kMSlots);
-    for (int pass = 0; pass < passes; ++pass) {
-        floatx4 acc[kMSlots][3];
-        int mt[kMSlots];          // wave-uniform M-tile of each slot
-        const float *wcol[kMSlots];
-        int wstride[kMSlots];
+    // this thread's rays of a chunk (absent probes and rays read a present one and are
+    // zeroed)
+    constexpr int kLoads = kP * kBlendChunk / 256;
+    float4 pv[kLoads];
+    auto fetch = [&](int k0) {
 #pragma unroll
-        for (int s = 0; s < kMSlots; ++s) {
-            mt[s] = pass * 4 * kMSlots + s * 4 + wave;
-            const bool irr = kStd ? s == 0 : mt[s] < mti;
-            wcol[s] = irr ? a.wt_i + mt[s] * 16 + row : a.wt_d + (mt[s] - mti) * 16 + row;
-            wstride[s] = irr ? Tpi : Tpd;
-#pragma unroll
-            for (int n = 0; n < 3; ++n) acc[s][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < kLoads; ++b) {
+            const int e = tid + 256 * b, q = e / kBlendChunk, kk = e - q * kBlendChunk;
+            pv[b] = a.payload[(size_t)s_pid[min(q, np - 1)] * a.R + min(k0 + kk, a.R - 1)];
         }
-        for (int k0 = 0; k0 < a.R; k0 += kBlendChunk) {
-            __syncthreads();
-            const int kc = min(kBlendChunk, a.R - k0);
-            // every read of the chunk issued at once (absent probes and rays read a
-            // present one and are zeroed)
-            constexpr int kLoads = kBlendProbes * kBlendChunk / 256;
-            float4 pv[kLoads];
+    };
+    const int passes = kMaps == kLargeMaps ? blend_passes(a.irr_res, a.depth_res) : 1;
+    for (int pass = 0; pass < passes; ++pass) {
+        floatx4 ai[kIS][kNi], ad[kDepthSlots][kNd];
+        // the slots' weights (irradiance tiles, then depth tiles) for a step and the next
+        GlobalBytes w[kSlots];
+        floatx4 a0[kSlots], a1[kSlots];
+        const int ti = pass * 4 * kIS + wave, td = pass * 4 * kDepthSlots + wave;
+        auto load_weights = [&](floatx4 (&av)[kSlots], int k) {
+            const uint32_t at = (uint32_t)(64 * min(k, a.R - 16) + 16 * lane);
 #pragma unroll
-            for (int b = 0; b < kLoads; ++b) {
-                const int e = tid + 256 * b, q = e / kBlendChunk, kk = e - q * kBlendChunk;
-                pv[b] = a.payload[(size_t)s_pid[min(q, np - 1)] * a.R + k0 + min(kk, kc - 1)];
+            for (int s = 0; s < kSlots; ++s)
+                av[s] = *(const __attribute__((address_space(1))) floatx4 *)(w[s] + at);
+        };
+        auto multiply = [&](const floatx4 (&av)[kSlots], int kk) {
+            floatx4 bi[kNi], bd[kNd];
+#pragma unroll
+            for (int n = 0; n < kNi; ++n)
+                bi[n] = *reinterpret_cast<const floatx4 *>(&sbuf[bi_off[n] + kk]);
+#pragma unroll
+            for (int n = 0; n < kNd; ++n) {
+                const floatx4 t = *reinterpret_cast<const floatx4 *>(&sbuf[bd_off[n] + kk]);
+                bd[n] = square ? t * t : t;
             }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+#pragma unroll
+                for (int s = 0; s < kIS; ++s)
+                    if (kStd || ti + 4 * s < mti)
+#pragma unroll
+                        for (int n = 0; n < kNi; ++n)
+                            ai[s][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][k], bi[n][k],
+                                                                            ai[s][n], 0, 0, 0);
+#pragma unroll
+                for (int s = 0; s < kDepthSlots; ++s)
+                    if (kStd || td + 4 * s < mtd)
+#pragma unroll
+                        for (int n = 0; n < kNd; ++n)
+                            ad[s][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kIS + s][k], bd[n][k],
+                                                                            ad[s][n], 0, 0, 0);
+            }
+        };
+        __syncthreads();
+        fetch(0);
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            // (slots past a map's last tile read that one's weights, unused)
+            const int tile = s < kIS ? min(ti + 4 * s, mti - 1) : min(td + 4 * (s - kIS), mtd - 1);
+            w[s] = (GlobalBytes)((s < kIS ? a.wt_i : a.wt_d) + (size_t)(16 * tile) * a.Rpad);
+        }
+        load_weights(a0, 0);
+#pragma unroll
+        for (int n = 0; n < kNi; ++n)
+#pragma unroll
+            for (int s = 0; s < kIS; ++s) ai[s][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int n = 0; n < kNd; ++n)
+#pragma unroll
+            for (int s = 0; s < kDepthSlots; ++s) ad[s][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k0 = 0; k0 < a.R; k0 += kBlendChunk) {
+            const int kc = min(kBlendChunk, a.R - k0);
+            if (k0) __syncthreads();
 #pragma unroll
             for (int b = 0; b < kLoads; ++b) {
                 const int e = tid + 256 * b, q = e / kBlendChunk, kk = e - q * kBlendChunk;
                 const float4 v = (q < np && kk < kc) ? pv[b] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                float *d = sx + q * 4 * kBlendPitch + kk;
-                d[0] = v.x; d[kBlendPitch] = v.y; d[2 * kBlendPitch] = v.z; d[3 * kBlendPitch] = v.w;
+                float *d = sbuf + q * 4 * kPitch + kk;
+                d[0] = v.x; d[kPitch] = v.y; d[2 * kPitch] = v.z; d[3 * kPitch] = v.w;
             }
             __syncthreads();
-            float a_cur[kMSlots], a_nxt[kMSlots];
-#pragma unroll
-            for (int s = 0; s < kMSlots; ++s)
-                a_cur[s] = (kStd || mt[s] < mtiles) ? wcol[s][(size_t)(k0 + krow) * wstride[s]] : 0.0f;
-            for (int kk = 0; kk < kc; kk += 4) {
-                const int kl = kk + krow;
-                if (kk + 4 < kc) {
-#pragma unroll
-                    for (int s = 0; s < kMSlots; ++s)
-                        a_nxt[s] = (kStd || mt[s] < mtiles) ? wcol[s][(size_t)(k0 + kl + 4) * wstride[s]]
-                                                            : 0.0f;
-                }
-                float bi[3], bd[2];
-#pragma unroll
-                for (int n = 0; n < 3; ++n) bi[n] = sx[bi_off[n] + kl];
-#pragma unroll
-                for (int n = 0; n < 2; ++n) {
-                    const float tv = sx[bd_off[n] + kl];
-                    bd[n] = bd_sq[n] ? tv * tv : tv;
-                }
-#pragma unroll
-                for (int s = 0; s < kMSlots; ++s) {
-                    if (kStd ? s == 0 : mt[s] < mti) {
-#pragma unroll
-                        for (int n = 0; n < 3; ++n)
-                            acc[s][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[s], bi[n], acc[s][n], 0, 0, 0);
-                    } else if (kStd || mt[s] < mtiles) {
-#pragma unroll
-                        for (int n = 0; n < 2; ++n)
-                            acc[s][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[s], bd[n], acc[s][n], 0, 0, 0);
-                    }
-                }
-#pragma unroll
-                for (int s = 0; s < kMSlots; ++s) a_cur[s] = a_nxt[s];
+            load_weights(a1, k0 + 16);
+            if (k0 + kBlendChunk < a.R) fetch(k0 + kBlendChunk);
+            for (int kk = 0; kk < kc; kk += 32) {
+                if (kk) load_weights(a1, k0 + kk + 16);
+                __builtin_amdgcn_sched_barrier(0);   // the reads go out before the products
+                multiply(a0, kk);
+                if (kk + 16 >= kc) break;
+                load_weights(a0, k0 + kk + 32);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a1, kk + 16);
             }
         }
-        // epilogue: lane holds D[4*krow + r][row] of each tile
-        if (kStd) {
-            blend_epilogue_std<false, 3, 2, true>(a, s_h, s_pid, np, wave, row, krow, acc, sbuf);
-            continue;
-        }
-#pragma unroll
-        for (int s = 0; s < kMSlots; ++s) {
-            if (!kStd && mt[s] >= mtiles) continue;
-            const bool irr = kStd ? s == 0 : mt[s] < mti;
-            const int res = irr ? ri : rd, T = irr ? Ti : Td, comps = irr ? 3 : 2;
-            const int side = irr ? si : sd;
-            const int m0 = (irr ? mt[s] : mt[s] - mti) * 16 + 4 * krow;
-            const float *norm = irr ? a.norm_i : a.norm_d;
-#pragma unroll
-            for (int n = 0; n < 3; ++n) {
-                if (!irr && n == 2) break;
-                const int col = n * 16 + row;
-                const int q = irr ? col / 3 : col >> 1;
-                const int c = irr ? col - 3 * q : col & 1;
-                if (q >= np) continue;
-                const size_t tile_floats = (size_t)side * side * comps;
-                const float *old_tile = (irr ? a.prev_irr : a.prev_depth) + (size_t)s_pid[q] * tile_floats;
-                float *new_tile = (irr ? a.new_irr : a.new_depth) + (size_t)s_pid[q] * tile_floats;
-                const float h = s_h[q];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = m0 + r;
-                    if (t >= T) continue;
-                    const int i = t % res, j = t / res;
-                    const float nrm = norm[t];
-                    const float old = old_tile[((j + 1) * side + (i + 1)) * comps + c];
-                    const float u = acc[s][n][r] * nrm;
-                    const float v = nrm < 0.0f ? old : fmaf(h, old - u, u);
-                    store_with_border(new_tile, res, comps, i, j, c, v);
-                }
-            }
-        }
+        if constexpr (kMaps == kLargeMaps)
+            blend_epilogue_direct<false>(a, s_h, s_pid, np, ti, td, row, krow, ai, ad);
+        else
+            blend_epilogue_lds<kStd, false>(a, s_h, s_pid, np, ti, td, row, krow, ai, ad, sbuf);
     }
     __syncthreads();
     if (tid < np && a.reject) a.reject[s_pid[tid]] = 0;
+}
+
+// (four workgroups per CU: 128 registers)
+template <int kMaps, int kP>
+__global__ __launch_bounds__(256, kMaps == kLargeMaps ? 2 : 4) void blend_kernel(BlendArgs a) {
+    blend32_block<kMaps, kP>(a, blockIdx.x * kP);
 }
 
 // Alg. 1 per probe: from the grid position, while the distance is below t1 (at most
@@ -1045,20 +1044,29 @@ hipError_t launch_shade(const TraceArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_blend(const BlendArgs &a, hipStream_t s) {
-    const dim3 grid(blocks_for(a.P, kBlendProbes)), block(256);
-    if (a.w16_i) {
-        if (a.irr_res == 8 && a.depth_res == 16)
-            hipLaunchKernelGGL(blend16_kernel<true>, grid, block, 0, s, a);
-        else
-            hipLaunchKernelGGL(blend16_kernel<false>, grid, block, 0, s, a);
-        return hipGetLastError();
-    }
-    if (a.irr_res == 8 && a.depth_res == 16)
-        hipLaunchKernelGGL(blend_kernel<true>, grid, block, 0, s, a);
+template <int kMaps, int kP>
+static hipError_t launch_blend_tile(const BlendArgs &a, hipStream_t s) {
+    const dim3 grid(blocks_for(a.P, kP)), block(256);
+    if (a.w16_i)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(blend16_kernel<kMaps, kP>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL(blend_kernel<false>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(blend_kernel<kMaps, kP>), grid, block, 0, s, a);
     return hipGetLastError();
+}
+
+// Probes per workgroup: 8, or 4 while 8 leave CUs of the 256-CU part without work. Tables,
+// blend and a copy of the maps, FP32 / precision form, with 16, 8 and 4 probes: at 1001
+// probes of 6x6 + 12x12 texels and 80 rays 23.9, 20.1, 17.7 / 25.3, 22.2, 20.1 us; 8x8 +
+// 16x16, 144 rays at 1000 probes 29.2, 22.5, 20.7 / 28.9, 20.4, 20.7 and at 4096 36.2, 31.0,
+// 35.3; 256 rays at 8192 60.1, 59.0, 82.7 / 51.6, 38.7, 54.5 and at 16384 104, 108, 144 /
+// 97.4, 70.7, 84.8 (a workgroup of 4 wastes 1/4 of its irradiance and half of its depth
+// products; one of 16 leaves fewer to overlap).
+hipError_t launch_blend(const BlendArgs &a, hipStream_t s) {
+    const bool small = a.P < 8 * 256;
+    if (blend_passes(a.irr_res, a.depth_res) > 1) return launch_blend_tile<kLargeMaps, 8>(a, s);
+    if (a.irr_res == 8 && a.depth_res == 16)
+        return small ? launch_blend_tile<kStdMaps, 4>(a, s) : launch_blend_tile<kStdMaps, 8>(a, s);
+    return small ? launch_blend_tile<kSmallMaps, 4>(a, s) : launch_blend_tile<kSmallMaps, 8>(a, s);
 }
 
 hipError_t launch_relocate(const TraceArgs &a, const RelocateArgs &r, hipStream_t s) {

@@ -110,8 +110,9 @@ bool finite_all(const float *v, int n) {
 struct RaySet {
     int R = 0, Rpad = 0;
     double *base = nullptr;          // [R][3] unrotated spherical-Fibonacci set
-    float *dirs = nullptr, *wt_i = nullptr, *wt_d = nullptr, *norm_i = nullptr, *norm_d = nullptr;
-    _Float16 *w16_i = nullptr;       // precision-form weight tables [T][Rpad]
+    float *dirs = nullptr, *norm_i = nullptr, *norm_d = nullptr;
+    float *wt_i = nullptr, *wt_d = nullptr;   // weight tables [T][Rpad], or those of the
+    _Float16 *w16_i = nullptr;       // precision form
     __bf16 *w16_d = nullptr;
     float4 *payload = nullptr;       // [P][R]
     int4 *hitq = nullptr;            // [P][R]
@@ -686,8 +687,15 @@ hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool listed = false) {
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     chk(dev_alloc(&r.base, 3 * (size_t)R));
     chk(dev_alloc(&r.dirs, 3 * (size_t)R));
-    chk(dev_alloc(&r.wt_i, (size_t)R * c->Tpi));
-    chk(dev_alloc(&r.wt_d, (size_t)R * c->Tpd));
+    r.Rpad = (R + 63) / 64 * 64;
+    const size_t wi = (size_t)c->Tpi * r.Rpad, wd = (size_t)c->Tpd * r.Rpad;
+    if (c->half) {
+        chk(dev_alloc(&r.w16_i, wi));
+        chk(dev_alloc(&r.w16_d, wd));
+    } else {
+        chk(dev_alloc(&r.wt_i, wi));
+        chk(dev_alloc(&r.wt_d, wd));
+    }
     chk(dev_alloc(&r.norm_i, c->Ti));
     chk(dev_alloc(&r.norm_d, c->Td));
     chk(dev_alloc(&r.payload, (size_t)c->P * R));
@@ -697,15 +705,12 @@ hipError_t alloc_set(sdfddgi_ctx *c, RaySet &r, int R, bool listed = false) {
     if (listed) chk(dev_alloc(&r.list, (size_t)c->P));
     if (e != hipSuccess) return e;
     chk(hipMemcpy(r.base, h_base.data(), 3 * (size_t)R * sizeof(double), hipMemcpyHostToDevice));
-    chk(hipMemsetAsync(r.wt_i, 0, (size_t)R * c->Tpi * sizeof(float), c->stream));
-    chk(hipMemsetAsync(r.wt_d, 0, (size_t)R * c->Tpd * sizeof(float), c->stream));
     if (c->half) {
-        r.Rpad = (R + 63) / 64 * 64;
-        chk(dev_alloc(&r.w16_i, (size_t)c->Tpi * r.Rpad));
-        chk(dev_alloc(&r.w16_d, (size_t)c->Tpd * r.Rpad));
-        if (e != hipSuccess) return e;
-        chk(hipMemsetAsync(r.w16_i, 0, (size_t)c->Tpi * r.Rpad * 2, c->stream));
-        chk(hipMemsetAsync(r.w16_d, 0, (size_t)c->Tpd * r.Rpad * 2, c->stream));
+        chk(hipMemsetAsync(r.w16_i, 0, wi * sizeof(_Float16), c->stream));
+        chk(hipMemsetAsync(r.w16_d, 0, wd * sizeof(__bf16), c->stream));
+    } else {
+        chk(hipMemsetAsync(r.wt_i, 0, wi * sizeof(float), c->stream));
+        chk(hipMemsetAsync(r.wt_d, 0, wd * sizeof(float), c->stream));
     }
     r.grid = trace_grid(c->device, c->P * R, c->half, c->analytic ? c->an.nprims : 0);
     return e;
@@ -717,8 +722,6 @@ TableArgs table_args(const sdfddgi_ctx *c, const RaySet &r, uint64_t seed, int n
     t.R = r.R;
     t.Ti = c->Ti;
     t.Td = c->Td;
-    t.Tpi = c->Tpi;
-    t.Tpd = c->Tpd;
     rotation_matrix(seed, t.q);
     t.sharp = (double)c->prm.depth_sharpness;
     t.base = r.base;
@@ -2223,8 +2226,6 @@ hipError_t batch_enqueue_front(sdfddgi_batch *b, int lane, const BatchTuning &t,
         ta.R = r.R;
         ta.Ti = 64;
         ta.Td = 256;
-        ta.Tpi = 64;
-        ta.Tpd = 256;
         ta.q_dev = reinterpret_cast<const double *>(b->frame_dev[cur]);
         ta.sharp = b->sharp;
         ta.base = r.base;

@@ -3,7 +3,7 @@ can go wrong: grids thinner and longer than a brick, ragged bricks, primitive co
 around the staging chunk, equal and non-finite primitives; maps whose float counts are
 not multiples of four; grids at the edges of the trace's cell bricks, too long for its
 24-bit products, and levels that are not nested; analytic scenes whose candidate cells
-hold one to too many primitives, and rays beyond them."""
+hold one to too many primitives, and rays beyond them; the blend's groups and tiles."""
 import sys
 
 import numpy as np
@@ -182,3 +182,43 @@ def test_analytic_candidate_cells(S, count, kind, t_max, spread):
                                                                   want_records=True)
     assert np.array_equal(rec[0], ref)
     assert np.array_equal(rec[1], ref)
+
+
+# The blend's tilings: a few probes, ragged groups of 4 and 8 at either side of where the group
+# changes, an odd number of 16-ray steps, rays that end within a chunk of 64, maps of one
+# texel tile up to the largest of one pass and beyond it in either map.
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("probes,rays,irr,depth", [
+    ((2, 2, 2), 16, 8, 16), ((3, 3, 3), 48, 2, 3), ((2, 3, 341), 64, 8, 16), ((2, 3, 341), 80, 5, 9),
+    ((32, 8, 8), 144, 8, 16), ((2, 5, 205), 272, 8, 16), ((2, 5, 205), 80, 11, 16),
+    ((5, 3, 3), 96, 12, 16), ((3, 5, 3), 112, 8, 17), ((13, 3, 2), 208, 3, 24), ((2, 2, 3), 64, 32, 32)])
+def test_blend_tilings(S, probes, rays, irr, depth, half):
+    import torch
+    announce(f"blend {probes} x {rays}, maps {irr} and {depth}, half={half}")
+    params = Params(rays_per_probe=rays, irr_res=irr, depth_res=depth)
+    none = Primitives(np.zeros(0, np.int32), np.zeros((0, 3)), np.zeros((0, 3)), np.zeros((0, 3)))
+    w = Workload("blend", none, [random_level((4, 4, 4), (0.0,) * 3, 1.0, 1)],
+                 ProbeGrid(probes, (0.5, 0.5, 0.5), (0.001, 0.01, 0.01)), params, [])
+    irr0, dep0 = scenegen.random_atlas(w.num_probes, params, seed=15)
+    pl = scenegen.random_payload(w.num_probes, rays, seed=16, t_max=params.t_max)
+    ctx = S.context_from_workload(w, flags=S.SDFDDGI_FLAG_FP16 if half else 0)
+    chk = oracle.Checker(w)
+    cuda = [torch.from_numpy(x).to("cuda:0") for x in (irr0, dep0, pl)]
+    check = np.unique(np.r_[0, w.num_probes - 1, np.random.default_rng(17).integers(
+        0, w.num_probes, 24)])
+    # binary32: sums of at most 272 products of one sign, (272 + 8) 2^-24 of the result;
+    # precision form: a payload and two weight roundings of 2^-11 / 2^-9 of the largest value
+    big = [np.pi * pl[..., :3].max(), np.array([pl[..., 3].max(), pl[..., 3].max() ** 2])]
+    for reset in (True, False):
+        S.sdfddgi_set_maps(ctx, cuda[0], cuda[1])
+        if reset:
+            S.sdfddgi_reset_history(ctx)
+        S.sdfddgi_blend(ctx, cuda[2], 99 + reset)
+        got = [m.cpu().numpy() for m in S.sdfddgi_get_maps(ctx)]
+        for p in check:
+            ref = chk.blend_probe(99 + reset, reset, pl[p], irr0[p], dep0[p])
+            for g, r, top, ulp in zip(got, ref, big, (2.0 ** -11, 2.0 ** -9)):
+                bound = 3 * ulp * top if half else 280 * 2.0 ** -24 * np.abs(r) + 1e-7 * np.mean(
+                    np.abs(r))
+                assert np.all(np.abs(g[p] - r) <= bound), (p, np.max(np.abs(g[p] - r) / bound))
+    S.sdfddgi_destroy(ctx)
