@@ -311,14 +311,25 @@ struct TrainArgs {
     int sequential;               // 1: samples 0..batch-1 in order; 0: SplitMix64 draws
     MlpPack mlp;
     float inv_n, head_weight, min_error;
-    float *grad;                  // [kMlpParams], accumulated (zero before the launch)
-    float *loss;                  // [1], accumulated
+    float *partial;               // [kTrainBlocks][kGradSlots]: each workgroup's sums
 };
 
-struct AdamArgs {
-    float *theta, *m, *v, *grad;  // grad is consumed and zeroed
-    int n;
+// Workgroups of a training step at most, and floats of each one's sums: the 40 weight
+// gradient tiles as their lanes hold them, [tile][lane][4], then the gradients of b2, b3
+// and b4 and the loss.
+constexpr int kTrainBlocks = 256;
+constexpr int kGradTiles = 40, kGradBias = kGradTiles * 256;
+constexpr int kGradSlots = kGradBias + 2 * kHidden + 64;
+
+struct UpdateArgs {
+    const float *partial;
+    int parts;                    // workgroups of the step
+    float *grad;                  // [kMlpParams + 1]: the sums; null: only the loss is kept
+    float *loss;                  // [1]
+    float *theta, *m, *v;         // Adam's step, unless theta is null
     float lr, beta1, beta2, eps, c1, c2;   // c1 = 1/(1-beta1^t), c2 = 1/(1-beta2^t)
+    __bf16 *fwd, *bwd;            // and its weights' places in the packs (see MlpPack)
+    float *bias;
 };
 
 hipError_t launch_probe_sdf(const TraceArgs &a, float *out, hipStream_t stream);
@@ -350,8 +361,9 @@ hipError_t launch_select_fallback(const uint8_t *reject, uint8_t *fb_flag, int P
                                   int *count, hipStream_t stream);
 hipError_t launch_examples(const ExampleArgs &a, hipStream_t stream);
 hipError_t launch_infer(const InferArgs &a, hipStream_t stream);
+int train_blocks(int batch);
 hipError_t launch_train(const TrainArgs &a, hipStream_t stream);
-hipError_t launch_adam(const AdamArgs &a, hipStream_t stream);
+hipError_t launch_update(const UpdateArgs &a, hipStream_t stream);
 hipError_t launch_zero_f32(float *dst, int64_t n, hipStream_t stream);
 
 // Scene baking (scene.hip). Primitive arrays are device copies; kind 0 sphere

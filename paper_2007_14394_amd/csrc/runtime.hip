@@ -248,6 +248,7 @@ struct sdfddgi_trainer {
     sdfddgi_train_config cfg{};
     int64_t step = 0;
     float *theta = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *loss = nullptr;
+    float *partial = nullptr;
     uint4 *fwd = nullptr, *bwd = nullptr;
     float *bias = nullptr;
 };
@@ -1776,7 +1777,7 @@ sdfddgi_status sdfddgi_trainer_destroy(sdfddgi_trainer *t) {
     (void)hipSetDevice(t->device);
     (void)hipStreamSynchronize(t->stream);
     t->loss = nullptr;  // the last element of the grad allocation, not an allocation
-    dev_free(t->theta); dev_free(t->m); dev_free(t->v); dev_free(t->grad);
+    dev_free(t->theta); dev_free(t->m); dev_free(t->v); dev_free(t->grad); dev_free(t->partial);
     dev_free(t->fwd); dev_free(t->bwd); dev_free(t->bias);
     delete t;
     return SDFDDGI_OK;
@@ -1808,6 +1809,7 @@ sdfddgi_status sdfddgi_trainer_create(const float *init, int32_t count,
     chk(dev_alloc(&t->m, kMlpParams));
     chk(dev_alloc(&t->v, kMlpParams));
     chk(dev_alloc(&t->grad, kMlpParams + 1));
+    chk(dev_alloc(&t->partial, (size_t)kTrainBlocks * kGradSlots));
     chk(dev_alloc(&t->fwd, kFwdEntries * 64));
     chk(dev_alloc(&t->bwd, kBwdEntries * 64));
     chk(dev_alloc(&t->bias, kBiasFloats));
@@ -1828,11 +1830,11 @@ sdfddgi_status sdfddgi_trainer_create(const float *init, int32_t count,
     return SDFDDGI_OK;
 }
 
+// The step's gradient, as its workgroups' sums, and what to do with them.
 static hipError_t run_train(sdfddgi_trainer *t, const float *features, const float *targets,
-                            int64_t count, int32_t batch, uint64_t seed, int sequential) {
+                            int64_t count, int32_t batch, uint64_t seed, int sequential,
+                            UpdateArgs u) {
     (void)hipGetLastError();
-    hipError_t e = launch_zero_f32(t->grad, kMlpParams + 1, t->stream);
-    if (e != hipSuccess) return e;
     TrainArgs a{};
     a.features = features;
     a.targets = targets;
@@ -1844,9 +1846,13 @@ static hipError_t run_train(sdfddgi_trainer *t, const float *features, const flo
     a.inv_n = (float)(1.0 / (double)batch);
     a.head_weight = t->cfg.head_weight;
     a.min_error = t->cfg.min_error;
-    a.grad = t->grad;
-    a.loss = t->loss;
-    return launch_train(a, t->stream);
+    a.partial = t->partial;
+    hipError_t e = launch_train(a, t->stream);
+    if (e != hipSuccess) return e;
+    u.partial = t->partial;
+    u.parts = train_blocks(batch);
+    u.loss = t->loss;
+    return launch_update(u, t->stream);
 }
 
 sdfddgi_status sdfddgi_trainer_gradient(sdfddgi_trainer *t, const float *features,
@@ -1856,7 +1862,9 @@ sdfddgi_status sdfddgi_trainer_gradient(sdfddgi_trainer *t, const float *feature
     if (!t) return lfail(SDFDDGI_EINVAL, "trainer is NULL");
     if (n < 1 || !features || !targets) return lfail(SDFDDGI_EINVAL, "need n >= 1 samples");
     hipError_t e = hipSetDevice(t->device);
-    if (e == hipSuccess) e = run_train(t, features, targets, n, n, 0, 1);
+    UpdateArgs u{};
+    u.grad = t->grad;
+    if (e == hipSuccess) e = run_train(t, features, targets, n, n, 0, 1, u);
     if (e == hipSuccess && grad)
         e = hipMemcpyAsync(grad, t->grad, kMlpParams * sizeof(float), hipMemcpyDeviceToHost,
                            t->stream);
@@ -1876,24 +1884,24 @@ sdfddgi_status sdfddgi_trainer_step(sdfddgi_trainer *t, const float *features,
         return lfail(SDFDDGI_EINVAL, "need count >= 1, batch >= 1 and both arrays");
     if (!(lr >= 0) || !std::isfinite(lr)) return lfail(SDFDDGI_EINVAL, "bad learning rate");
     hipError_t e = hipSetDevice(t->device);
-    if (e == hipSuccess) e = run_train(t, features, targets, count, batch, seed, 0);
     if (e == hipSuccess) {
-        ++t->step;
-        AdamArgs a{};
-        a.theta = t->theta;
-        a.m = t->m;
-        a.v = t->v;
-        a.grad = t->grad;
-        a.n = kMlpParams;
-        a.lr = lr;
-        a.beta1 = t->cfg.beta1;
-        a.beta2 = t->cfg.beta2;
-        a.eps = t->cfg.eps;
-        a.c1 = (float)(1.0 / (1.0 - std::pow((double)t->cfg.beta1, (double)t->step)));
-        a.c2 = (float)(1.0 / (1.0 - std::pow((double)t->cfg.beta2, (double)t->step)));
-        e = launch_adam(a, t->stream);
+        const double step = (double)(t->step + 1);
+        UpdateArgs u{};
+        u.theta = t->theta;
+        u.m = t->m;
+        u.v = t->v;
+        u.lr = lr;
+        u.beta1 = t->cfg.beta1;
+        u.beta2 = t->cfg.beta2;
+        u.eps = t->cfg.eps;
+        u.c1 = (float)(1.0 / (1.0 - std::pow((double)t->cfg.beta1, step)));
+        u.c2 = (float)(1.0 / (1.0 - std::pow((double)t->cfg.beta2, step)));
+        u.fwd = reinterpret_cast<__bf16 *>(t->fwd);
+        u.bwd = reinterpret_cast<__bf16 *>(t->bwd);
+        u.bias = t->bias;
+        e = run_train(t, features, targets, count, batch, seed, 0, u);
+        if (e == hipSuccess) ++t->step;
     }
-    if (e == hipSuccess) e = launch_pack_mlp(t->theta, t->fwd, t->bwd, t->bias, t->stream);
     if (e == hipSuccess && loss) {
         e = hipMemcpyAsync(loss, t->loss, sizeof(float), hipMemcpyDeviceToHost, t->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(t->stream);

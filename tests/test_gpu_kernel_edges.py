@@ -3,7 +3,8 @@ can go wrong: grids thinner and longer than a brick, ragged bricks, primitive co
 around the staging chunk, equal and non-finite primitives; maps whose float counts are
 not multiples of four; grids at the edges of the trace's cell bricks, too long for its
 24-bit products, and levels that are not nested; analytic scenes whose candidate cells
-hold one to too many primitives, and rays beyond them; the blend's groups and tiles."""
+hold one to too many primitives, and rays beyond them; the blend's groups and tiles; training
+steps and inference around their workgroups' sizes."""
 import sys
 
 import numpy as np
@@ -222,3 +223,56 @@ def test_blend_tilings(S, probes, rays, irr, depth, half):
                     np.abs(r))
                 assert np.all(np.abs(g[p] - r) <= bound), (p, np.max(np.abs(g[p] - r) / bound))
     S.sdfddgi_destroy(ctx)
+
+
+# A training step's samples over the workgroups (64 each, up to 256 of them, then strided),
+# its sums, and the weights that Adam's step leaves in the packs.
+@pytest.mark.parametrize("n", [1, 64, 65, 4000, 16385, 20000])
+def test_training_parts(S, n):
+    import torch
+    announce(f"training on {n} samples")
+    rng = np.random.default_rng(n)
+    th = rng.normal(0, 0.1, oracle.MLP_PARAMS).astype(np.float32)
+    x = rng.normal(0, 0.5, (n, 16)).astype(np.float32)
+    tg = np.column_stack([rng.normal(0, 0.3, (n, 3)), rng.uniform(0.3, 2.0, n)]).astype(np.float32)
+    xd, td = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(tg).to("cuda:0")
+    make = lambda p: S.sdfddgi_trainer_create(p, head_weight=0.3, min_error=1e-4)
+    tr = make(th)
+    loss, g = S.sdfddgi_trainer_gradient(tr, xd, td)
+    # the mean over parts is the mean of the parts' means, up to the sums' binary32 rounding:
+    # 14 roundings deep, of partial sums no larger than the sum of the samples' magnitudes
+    cut = [0, n // 3, n] if n > 2 else [0, n]
+    parts = [(b - a, S.sdfddgi_trainer_gradient(tr, xd[a:b].contiguous(), td[a:b].contiguous()))
+             for a, b in zip(cut, cut[1:])]
+    ref = sum(k * p[1].astype(np.float64) for k, p in parts) / n
+    # (each part's bfloat16 gradients are those of 1/n scaled: one more rounding of 2^-8)
+    assert np.linalg.norm(g - ref) <= 2.0 ** -7 * np.linalg.norm(ref)
+    assert abs(loss - sum(k * p[0] for k, p in parts) / n) <= 2e-6 * abs(loss)
+    for seed in (3, 4):
+        S.sdfddgi_trainer_step(tr, xd, td, n, seed, 1e-3)
+    th2 = S.sdfddgi_trainer_get_params(tr)
+    assert np.isfinite(th2).all() and not np.array_equal(th2, th)
+    loss_a, g_a = S.sdfddgi_trainer_gradient(tr, xd, td)
+    loss_b, g_b = S.sdfddgi_trainer_gradient(make(th2), xd, td)
+    assert loss_a == loss_b and np.array_equal(g_a, g_b)
+
+
+# Rows of the network alone: part of a tile, of a wave's four tiles, more than the grid, and
+# arrays aligned to four bytes only.
+@pytest.mark.parametrize("n", [1, 15, 64, 65, 300000])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_infer_rows(S, n, offset):
+    import torch
+    announce(f"inference on {n} rows, offset {offset}")
+    rng = np.random.default_rng(n)
+    th = rng.normal(0, 0.1, oracle.MLP_PARAMS).astype(np.float32)
+    x = rng.normal(0, 0.5, (n, 16)).astype(np.float32)
+    den = S.sdfddgi_denoiser_create(th, 1.0, 1.0)
+    flat = torch.zeros(16 * n + offset, device="cuda:0")
+    xd = flat[offset:].view(n, 16)
+    xd.copy_(torch.from_numpy(x))
+    out = S.sdfddgi_denoiser_infer(den, xd).cpu().numpy()
+    pick = np.unique(np.r_[0, n - 1, rng.integers(0, n, 40)])
+    ref = oracle.mlp_forward(th.astype(np.float64), x[pick].astype(np.float64))
+    # the same bfloat16 operands (an activation may round the other way): 2^-8 of the scale
+    assert np.max(np.abs(out[pick] - ref)) <= 2.0 ** -8 * max(1.0, np.abs(ref).max())
