@@ -72,8 +72,9 @@
  *     context owns, so the caller may free them once create returns.
  *   - GPU work goes on the stream given to sdfddgi_create, in order, and is
  *     asynchronous: results are valid once the caller synchronises that stream.
- *     The one exception is internal: back-to-back sdfddgi_update_frame calls
- *     run each frame's tables and primary trace on a side stream of the context
+ *     The one exception is internal: consecutive sdfddgi_update_frame calls
+ *     (with no others than sdfddgi_get_maps and sdfddgi_sample_irradiance in
+ *     between) run each frame's tables and primary trace on a side stream of the context
  *     and, on grid contexts, the atlas-independent half of its hit shading
  *     (normal, shadow ray, albedo) on a second one (default priority), both
  *     overlapping the previous frame's lookups and blend, and join them back
@@ -206,8 +207,9 @@ sdfddgi_status sdfddgi_create_analytic(int32_t nprims, const int32_t *kind, cons
 /* One frame of the probe update of Sec. 3.3 for every probe (steps 1-5
  * above). Reads the current maps as the previous frame, writes the other
  * buffer pair, then makes it current. Clears every probe's reject flag.
- * Consecutive calls with no other call on the context in between overlap (see
- * the stream convention above); the results are the same as one at a time.
+ * Consecutive calls with no other call on the context in between, except those
+ * that only read the maps (sdfddgi_get_maps, sdfddgi_sample_irradiance), overlap
+ * (see the stream convention above); the results are the same as one at a time.
  * A context created with SDFDDGI_FLAG_RECORD_RAYS never overlaps frames. */
 sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *ctx, const sdfddgi_light *light,
                                     uint64_t rotation_seed);
@@ -493,10 +495,10 @@ sdfddgi_status sdfddgi_batch_create(const sdfddgi_batch_scene *scenes, int32_t c
 /* One frame for every scene: lights (host [count]) and the shared rotation seed.
  * Enqueues two graph replays: the tables, the primary trace and the atlas-independent
  * half of the hit shading on a side stream of the batch (default priority) and the
- * lookups and blend on the batch's stream, joined by an event. Consecutive calls overlap
- * (a frame's side part runs beside the previous frame's lookups and blend); any other call on the batch
- * in between makes the next frame wait for everything before it. Results are
- * valid once the caller synchronises the batch's stream. */
+ * lookups and blend on the batch's stream, joined by an event. Consecutive calls
+ * overlap (a frame's side part runs beside the previous frame's lookups and blend);
+ * any other call on the batch in between makes the next frame wait for everything
+ * before it. Results are valid once the caller synchronises the batch's stream. */
 sdfddgi_status sdfddgi_batch_update_frame(sdfddgi_batch *b, const sdfddgi_light *lights,
                                           uint64_t rotation_seed);
 

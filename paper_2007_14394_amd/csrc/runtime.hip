@@ -109,6 +109,7 @@ bool finite_all(const float *v, int n) {
 // rays (rays_per_probe) and the learned form's low ray count.
 struct RaySet {
     int R = 0, Rpad = 0;
+    bool captured = false;           // the done event was last recorded in a stream capture
     double *base = nullptr;          // [R][3] unrotated spherical-Fibonacci set
     float *dirs = nullptr, *norm_i = nullptr, *norm_d = nullptr;
     float *wt_i = nullptr, *wt_d = nullptr;   // weight tables [T][Rpad], or those of the
@@ -180,8 +181,10 @@ struct sdfddgi_ctx {
     // half and blend. A frame's side work waits for the done event of the ray set it
     // traces into (recorded after the blend of the frame before the previous one);
     // ev_primary joins the side stream to side2 (or, unsplit, to the caller's
-    // stream) and the set's ready event side2 to the caller's. Any other call in
-    // between makes the next frame wait for everything before it (serialize_next).
+    // stream) and the set's ready event side2 to the caller's. Calls that only read
+    // the maps (get_maps, sample_irradiance) may come in between; any other makes
+    // the next frame wait for everything before it (serialize_next). A small room read
+    // back after every frame: 191 -> 126 us a frame.
     hipStream_t side = nullptr;
     hipEvent_t ev_primary = nullptr, ev_tail = nullptr;
     bool serialize_next = true;
@@ -829,16 +832,28 @@ TraceArgs trace_pass(const TraceArgs &base, const RaySet &r, int *counters, int 
     return t;
 }
 
-sdfddgi_status check_ctx(sdfddgi_ctx *c) {
+// reads_maps: the call only reads the current maps, on the caller's stream. A frame's side
+// chains touch no map but those that its predecessor's work on that stream is done with, so
+// the next frame may overlap such a call as it may overlap the frame before.
+sdfddgi_status check_ctx(sdfddgi_ctx *c, bool reads_maps = false) {
     if (!c) return SDFDDGI_EINVAL;
     c->err.clear();
     // launch status is read with hipGetLastError: drop a failure some other code left
     (void)hipGetLastError();
-    // the next plain frame waits for whatever this call enqueues
-    c->serialize_next = true;
+    // the next frame waits for whatever this call enqueues
+    if (!reads_maps) c->serialize_next = true;
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     return SDFDDGI_OK;
+}
+
+// Whether the caller's stream is being captured (or cannot be asked): the frame then waits
+// for the stream's work so far, which draws the side streams into the capture.
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &status);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
 // Light direction normalised in binary64 and rounded once; EINVAL on bad input.
@@ -1195,9 +1210,11 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
                                     uint64_t rotation_seed) {
     // overlap with the previous frame only when nothing else came in between and no
     // per-ray records are kept (they are one buffer for both frames)
-    const bool serial = !c || c->serialize_next || c->records || c->learned_chain;
+    bool serial = !c || c->serialize_next || c->records || c->learned_chain;
     sdfddgi_status st = check_ctx(c);
     if (st != SDFDDGI_OK) return st;
+    const bool capture = capturing(c->stream);
+    serial = serial || capture || c->spare.captured;
     c->learned_chain = false;
     float l[3], rad[3];
     if ((st = light_of(c, light, l, rad)) != SDFDDGI_OK) return st;
@@ -1274,6 +1291,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     TRY_HIP(c, ev.mark(5), "event");
     TRY_HIP(c, ev.mark(10), "event");
     TRY_HIP(c, hipEventRecord(r.done, c->stream), "event");
+    r.captured = capture;
     frame_done(c, false);
     std::swap(c->main, c->spare);
     c->cur = nxt;
@@ -1301,7 +1319,7 @@ sdfddgi_status sdfddgi_blend(sdfddgi_ctx *c, const float *payload, uint64_t rota
 
 sdfddgi_status sdfddgi_sample_irradiance(sdfddgi_ctx *c, const float *points,
                                          const float *normals, int64_t n, float *out_rgb) {
-    sdfddgi_status st = check_ctx(c);
+    sdfddgi_status st = check_ctx(c, true);
     if (st != SDFDDGI_OK) return st;
     if (n < 0) return fail(c, SDFDDGI_EINVAL, "negative count");
     if (n == 0) return SDFDDGI_OK;
@@ -1319,7 +1337,7 @@ sdfddgi_status sdfddgi_sample_irradiance(sdfddgi_ctx *c, const float *points,
 }
 
 sdfddgi_status sdfddgi_get_maps(sdfddgi_ctx *c, float *irr, float *depth) {
-    sdfddgi_status st = check_ctx(c);
+    sdfddgi_status st = check_ctx(c, true);
     if (st != SDFDDGI_OK) return st;
     TRY_HIP(c, launch_copy_pair(irr, c->irr[c->cur], irr ? c->irr_floats : 0, depth,
                                 c->depth[c->cur], depth ? c->depth_floats : 0, c->stream),
@@ -1580,9 +1598,11 @@ static sdfddgi_status check_learned(sdfddgi_ctx *c, const sdfddgi_denoiser *d) {
 
 sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denoiser *d,
                                             const sdfddgi_light *light, uint64_t rotation_seed) {
-    const bool serial = !c || c->serialize_next || c->records || !c->learned_chain;
+    bool serial = !c || c->serialize_next || c->records || !c->learned_chain;
     sdfddgi_status st = check_ctx(c);
     if (st != SDFDDGI_OK) return st;
+    const bool capture = capturing(c->stream);
+    serial = serial || capture || c->low[c->learned_index % 2].captured;
     c->learned_chain = false;
     if ((st = check_learned(c, d)) != SDFDDGI_OK) return st;
     float l[3], rad[3];
@@ -1701,6 +1721,7 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     TRY_HIP(c, hipEventRecord(fb.done, c->stream), "event");
     TRY_HIP(c, ev.mark(10), "event");
     TRY_HIP(c, hipEventRecord(c->ev_end, c->stream), "event");
+    lo.captured = capture;
     ++c->learned_index;
     frame_done(c, true);
     c->last_learned = k;

@@ -276,3 +276,44 @@ def test_infer_rows(S, n, offset):
     ref = oracle.mlp_forward(th.astype(np.float64), x[pick].astype(np.float64))
     # the same bfloat16 operands (an activation may round the other way): 2^-8 of the scale
     assert np.max(np.abs(out[pick] - ref)) <= 2.0 ** -8 * max(1.0, np.abs(ref).max())
+
+
+# Frames with nothing but reads of the maps in between overlap as back-to-back ones do; what
+# is read, and the next frames, must be those of a context that never overlaps (it keeps
+# records). Plain, analytic and learned frames, and switches between them.
+@pytest.mark.parametrize("form", ["plain", "fp16", "analytic", "learned"])
+def test_map_reads_between_overlapping_frames(S, form):
+    import torch
+    from paper_2007_14394_amd import denoiser_weights
+    announce(f"map reads between frames, {form}")
+    w = scenegen.config2(2, probes=8192, frames=8, rays=64, grid=64)
+    more = dict(analytic=dict(analytic=True), learned=dict(learned_rays=16, fallback_error=0.05))
+    fl = S.SDFDDGI_FLAG_FP16 if form == "fp16" else 0
+    ctxs = [S.context_from_workload(w, flags=fl, **more.get(form, {})),
+            S.context_from_workload(w, flags=fl | S.SDFDDGI_FLAG_RECORD_RAYS, **more.get(form, {}))]
+    net = denoiser_weights.load()
+    den = S.sdfddgi_denoiser_create(net["params"], net["irr_scale"], net["depth_scale"])
+    rng = np.random.default_rng(4)
+    pts = torch.from_numpy(rng.uniform(-20, 20, (5000, 3)).astype(np.float32)).to("cuda:0")
+    nrm = torch.from_numpy(rng.normal(size=(5000, 3)).astype(np.float32)).to("cuda:0")
+    got = []
+    for ctx in ctxs:
+        reads = []
+        for k, fr in enumerate(w.frames):
+            args = (fr.dir_to_light, fr.radiance_rgb, fr.rotation_seed)
+            if form == "learned" and k != 5:   # and one plain frame among the learned ones
+                S.sdfddgi_update_frame_learned(ctx, den, *args)
+            else:
+                S.sdfddgi_update_frame(ctx, *args)
+            if k != 3:
+                reads += [m.clone() for m in S.sdfddgi_get_maps(ctx)]
+            if k in (2, 3, 6):
+                reads.append(S.sdfddgi_sample_irradiance(ctx, pts, nrm).clone())
+            if k == 4:
+                S.sdfddgi_reset_history(ctx)
+                reads += [m.clone() for m in S.sdfddgi_get_maps(ctx)]
+        got.append(reads)
+        S.sdfddgi_destroy(ctx)
+    assert len(got[0]) == len(got[1])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
