@@ -152,8 +152,8 @@ __global__ __launch_bounds__(256) void batch_primary_kernel(BatchArgs a, int chu
                     const bool inside = !out && k == 0 && dist < 0.0f;
                     if (out || inside) {
                         const BatchScene &s = s_sc[sc];
-                        a.payload[ray] = inside ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
-                                                : make_float4(s.sky0, s.sky1, s.sky2, s.t_max);
+                        store_streamed(&a.payload[ray], inside ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
+                                                : make_float4(s.sky0, s.sky1, s.sky2, s.t_max));
                     } else {
                         hit = true;
                         entry = make_int4(ray, __float_as_int(t),
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(256) void batch_shade_kernel(BatchArgs a) {
         out.y = g1.y * inv_pi * (lt[4] * g0.w + s.gain * ind.y);
         out.z = g1.z * inv_pi * (lt[5] * g0.w + s.gain * ind.z);
         out.w = ht;
-        a.payload[e.x] = out;
+        store_streamed(&a.payload[e.x], out);
     }
 }
 

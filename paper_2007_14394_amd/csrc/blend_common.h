@@ -282,7 +282,8 @@ __device__ __forceinline__ void blend16_block(const BlendArgs &a, int pb) {
 #pragma unroll
         for (int b = 0; b < kLoads; ++b) {
             const int e = tid + 256 * b, q = e / kChunk, kk = e - q * kChunk;
-            pv[b] = a.payload[(size_t)s_pid[min(q, np - 1)] * a.R + min(k0 + kk, a.R - 1)];
+            pv[b] = load_streamed(a.payload + (size_t)s_pid[min(q, np - 1)] * a.R +
+                                  min(k0 + kk, a.R - 1));
         }
     };
     const int passes = kMaps == kLargeMaps ? blend_passes(a.irr_res, a.depth_res) : 1;

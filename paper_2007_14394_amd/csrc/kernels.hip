@@ -188,7 +188,7 @@ template <typename Args>
 __device__ __forceinline__ void write_ray(const Args &a, int ray, float4 out, int kind,
                                           int level, int steps, int vis, int shadow_steps,
                                           float n0, float n1, float n2) {
-    a.payload[ray] = out;
+    store_streamed(&a.payload[ray], out);
     write_record(a, ray, out.w, kind, level, steps, vis, shadow_steps, n0, n1, n2);
 }
 
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(256) void shade_kernel(TraceArgs a) {
             const float hx2 = fmaf(ht, a.dirs[3 * i + 2], a.probe_pos[3 * p + 2]);
             ind = interp_irradiance(a.prev_irr, a.irr_res, a.pg, hx0, hx1, hx2, g0.x, g0.y, g0.z);
         }
-        a.payload[ray] = shade_hit(a, make_float3(g1.x, g1.y, g1.z), g0.w, ind, ht);
+        store_streamed(&a.payload[ray], shade_hit(a, make_float3(g1.x, g1.y, g1.z), g0.w, ind, ht));
     }
 }
 
@@ -684,7 +684,8 @@ __device__ __forceinline__ void blend32_block(const BlendArgs &a, int pb) {
 #pragma unroll
         for (int b = 0; b < kLoads; ++b) {
             const int e = tid + 256 * b, q = e / kBlendChunk, kk = e - q * kBlendChunk;
-            pv[b] = a.payload[(size_t)s_pid[min(q, np - 1)] * a.R + min(k0 + kk, a.R - 1)];
+            pv[b] = load_streamed(a.payload + (size_t)s_pid[min(q, np - 1)] * a.R +
+                                  min(k0 + kk, a.R - 1));
         }
     };
     const int passes = kMaps == kLargeMaps ? blend_passes(a.irr_res, a.depth_res) : 1;
