@@ -982,9 +982,10 @@ static int persistent_blocks(const void *kernel, int device, int64_t rays, int m
 // 494, 502 us in binary32 and 481, 379, 358, 374, 394, 413 in binary16; the hit shading
 // with 1, 2, 3, 4 162, 144, 155, 166 us. Beside the other frames' work (four frames and
 // their maps): primary 3 and 4 blocks 2.65 and 2.77 ms in binary32, 2.23 and 2.23 in
-// binary16; hit shading 1, 2, 3 blocks 2.77, 2.79, 2.93 ms.
+// binary16; hit shading 1, 2, 3 blocks 2.77, 2.79, 2.93 ms. The trace of primitives needs
+// no lines: 2, 3, 4, 5 blocks 388, 372, 341, 337 us a frame (16384 x 64).
 constexpr int kPrimaryBlocksPerCu = 4;
-constexpr int kPrimaryBlocksPerCuOverlapped[2] = {3, 4};  // binary32, binary16 SDF
+constexpr int kPrimaryBlocksPerCuOverlapped[2] = {3, 4};  // binary32 SDF; binary16, primitives
 constexpr int kHitsBlocksPerCu = 2;
 constexpr int kHitsBlocksPerCuOverlapped = 1;
 
@@ -997,7 +998,7 @@ TraceGrid trace_grid(int device, int64_t rays, bool half, int analytic_prims) {
                               : (const void *)primary_kernel<kSdfGrid32>;
     g.primary_blocks = persistent_blocks(pk, device, rays, kPrimaryBlocksPerCu, lds);
     g.primary_blocks_overlapped =
-        persistent_blocks(pk, device, rays, kPrimaryBlocksPerCuOverlapped[half ? 1 : 0], lds);
+        persistent_blocks(pk, device, rays, kPrimaryBlocksPerCuOverlapped[half || analytic ? 1 : 0], lds);
     const void *hk = analytic ? (const void *)hits_kernel<kSdfAnalytic>
                      : half   ? (const void *)hits_kernel<kSdfGrid16>
                               : (const void *)hits_kernel<kSdfGrid32>;
