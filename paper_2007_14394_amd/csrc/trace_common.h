@@ -156,21 +156,52 @@ __device__ __forceinline__ float distance_inside(GlobalBytes cells, const LevelC
     return lerp_corners(load_corners<kHalf, kWide>(cells, d, i0, i1, i2), f0, f1, f2);
 }
 
-// Central differences at +-spacing/2 on the hit's level, normalised. kUnroll: axes whose
-// samples are in flight at once (1: a third of the registers).
-template <bool kHalf, int kUnroll = 3>
+// Central differences at +-spacing/2 on the hit's level, normalised. Half a cell either way,
+// one of an axis's two samples lies in x's own cell (but for rounding, and at the level's
+// borders, where both may or neither), whose corners are read once for all three: four
+// cells' reads instead of six, and fewer places to find. Of the frames of 24 scenes, bound by
+// the lines that their hits and traces draw through the L1, 6.58 -> 6.41 ms for four; one
+// axis at a time, in fewer registers, 6.49.
+template <bool kHalf>
 __device__ __forceinline__ void hit_normal(GlobalBytes cells, const LevelCells &d, int wide, float x0,
                                            float x1, float x2, float w0, float w1, float w2,
                                            float &n0, float &n1, float &n2) {
     const float h = d.half;
     float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f;
-#pragma unroll kUnroll
+    int i0, i1, i2;
+    float f0, f1, f2;
+    cell_of((x0 - d.org0) * d.inv, (float)d.cmax0, i0, f0);
+    cell_of((x1 - d.org1) * d.inv, (float)d.cmax1, i1, f1);
+    cell_of((x2 - d.org2) * d.inv, (float)d.cmax2, i2, f2);
+    auto corners = [&](int c0, int c1, int c2) {
+        return wide ? load_corners<kHalf, true>(cells, d, c0, c1, c2)
+                    : load_corners<kHalf, false>(cells, d, c0, c1, c2);
+    };
+    const Corners own = corners(i0, i1, i2);
+#pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        const float p0 = x0 + (ax == 0 ? h : 0.0f), m0 = x0 - (ax == 0 ? h : 0.0f);
-        const float p1 = x1 + (ax == 1 ? h : 0.0f), m1 = x1 - (ax == 1 ? h : 0.0f);
-        const float p2 = x2 + (ax == 2 ? h : 0.0f), m2 = x2 - (ax == 2 ? h : 0.0f);
-        const float g = sample_at<kHalf>(cells, d, wide, p0, p1, p2) -
-                        sample_at<kHalf>(cells, d, wide, m0, m1, m2);
+        const float x = ax == 0 ? x0 : ax == 1 ? x1 : x2;
+        const float org = ax == 0 ? d.org0 : ax == 1 ? d.org1 : d.org2;
+        const float cmax = (float)(ax == 0 ? d.cmax0 : ax == 1 ? d.cmax1 : d.cmax2);
+        const int i = ax == 0 ? i0 : ax == 1 ? i1 : i2;
+        int ip, im;
+        float fp, fm;
+        cell_of((x + h - org) * d.inv, cmax, ip, fp);
+        cell_of((x - h - org) * d.inv, cmax, im, fm);
+        // the sample in x's own cell (the minus one if neither is) and the other
+        const bool plus = ip == i;
+        const int far = plus ? im : ip;
+        auto along = [&](int c) {
+            return corners(ax == 0 ? c : i0, ax == 1 ? c : i1, ax == 2 ? c : i2);
+        };
+        const Corners other = along(far);
+        Corners near = own;
+        if (!plus && im != i) near = along(im);
+        auto at = [&](const Corners &c, float f) {
+            return lerp_corners(c, ax == 0 ? f : f0, ax == 1 ? f : f1, ax == 2 ? f : f2);
+        };
+        const float a = at(near, plus ? fp : fm), b = at(other, plus ? fm : fp);
+        const float g = plus ? a - b : b - a;
         g0 = ax == 0 ? g : g0;
         g1 = ax == 1 ? g : g1;
         g2 = ax == 2 ? g : g2;
