@@ -130,7 +130,7 @@ def ray_statistics(S, w, frames):
 def gather_peaks(S, torch):
     """Throughput of independent random 32-byte gathers (two adjacent 16-byte loads,
     the trace sampler's access) from device buffers sized for the L2 (4 MiB), the
-    Infinity Cache (128 MiB, about the binary32 cascade's 132 MB of corner quads)
+    Infinity Cache (128 MiB, about the binary32 cascade's 120 MB of cell bricks)
     and HBM (1 GiB): the trace's second roofline denominator."""
     out = {}
     threads, reads = 1 << 20, 64
@@ -606,8 +606,8 @@ def main():
         out["ray_stats"] = {"primary_steps": st["prim"], "shadow_steps": st["shadow"],
                             "hit_fraction": st["hits"]}
         if dom["unit"] == "GB/s":
-            # second denominator: measured gather peaks. The trace's 132 MB of corner
-            # quads exceed the L2, so its ceiling lies between random gathers beyond
+            # second denominator: measured gather peaks. The trace's 120 MB of cell
+            # bricks exceed the L2, so its ceiling lies between random gathers beyond
             # the L2 (no locality) and gathers the L2 serves (full locality).
             stage("gather peaks")
             peaks = gather_peaks(S, torch)

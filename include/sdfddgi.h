@@ -579,8 +579,8 @@ sdfddgi_status sdfddgi_analytic_destroy(sdfddgi_analytic *an);
 /* ------------------------------------------------------------ measurement --
  * The gather throughput of the trace's access pattern, the second roofline
  * denominator of the sphere trace beside HBM bandwidth (the trace reads each
- * sample's eight corners as two adjacent 16-byte corner quads, at positions the
- * rays scatter over the grid). Launches threads (1..2^30) threads on hip_stream,
+ * sample's eight corners as two 16-byte loads from one 128-byte line, at positions
+ * the rays scatter over the grid). Launches threads (1..2^30) threads on hip_stream,
  * each reading `reads` (a multiple of 8 in 8..4096) independent 32-byte records
  * of the device buffer buf (bytes = 32 x a power of two, at most 64 GiB) at
  * indices from a counter-based hash of (seed, thread, read). sink: a device

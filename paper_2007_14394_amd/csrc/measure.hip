@@ -1,7 +1,7 @@
 // Measurement kernel: the gather throughput the trace's sampler pattern can reach,
 // the second roofline denominator of the trace (beside HBM bandwidth). Each
-// thread reads `reads` records of 32 bytes (two adjacent 16-byte loads: the
-// layout of one trilinear sample's two corner quads) at indices from a
+// thread reads `reads` records of 32 bytes (two adjacent 16-byte loads, what one
+// trilinear sample reads of its brick's line) at indices from a
 // counter-based hash, independent of one another so that many are in flight, and
 // folds them into a value that is stored only under a condition the data never
 // meets (so no load is dead code).
