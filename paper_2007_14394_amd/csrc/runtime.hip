@@ -13,6 +13,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -183,7 +184,9 @@ struct sdfddgi_ctx {
     // ev_primary joins the side stream to side2 (or, unsplit, to the caller's
     // stream) and the set's ready event side2 to the caller's. Calls that only read
     // the maps (get_maps, sample_irradiance) may come in between; any other makes
-    // the next frame wait for everything before it (serialize_next). A small room read
+    // the next frame wait for everything before it (serialize_next), on every side
+    // stream, also those that only later frames use: what such a call touched (a set's
+    // tables, the probes' positions) no set's event tells of. A small room read
     // back after every frame: 191 -> 126 us a frame.
     hipStream_t side = nullptr;
     hipEvent_t ev_primary = nullptr, ev_tail = nullptr;
@@ -856,6 +859,18 @@ bool capturing(hipStream_t s) {
     return e != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
+// The start of a serial frame: `used`, the side streams that it launches on, after all
+// work on the caller's stream so far, and so the context's other side streams. (Those are
+// left out of a capture, which they would not join again.)
+hipError_t order_sides(sdfddgi_ctx *c, std::initializer_list<hipStream_t> used, bool capture) {
+    hipError_t e = hipEventRecord(c->ev_tail, c->stream);
+    for (hipStream_t s : {c->side, c->side2, c->side3}) {
+        const bool in_use = std::find(used.begin(), used.end(), s) != used.end();
+        if (e == hipSuccess && s && (in_use || !capture)) e = hipStreamWaitEvent(s, c->ev_tail, 0);
+    }
+    return e;
+}
+
 // Light direction normalised in binary64 and rounded once; EINVAL on bad input.
 sdfddgi_status light_of(sdfddgi_ctx *c, const sdfddgi_light *light, float l[3], float rad[3]) {
     if (!light) return fail(c, SDFDDGI_EINVAL, "light is NULL");
@@ -1233,8 +1248,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     // done event; so wait for that (the trace then starts as soon as its set is
     // free), or, when serial, for everything enqueued so far
     if (serial) {
-        TRY_HIP(c, hipEventRecord(c->ev_tail, c->stream), "event");
-        TRY_HIP(c, hipStreamWaitEvent(c->side, c->ev_tail, 0), "stream wait");
+        TRY_HIP(c, order_sides(c, {c->side}, capture), "stream wait");
     } else {
         TRY_HIP(c, hipStreamWaitEvent(c->side, r.done, 0), "stream wait");
     }
@@ -1615,9 +1629,7 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     hipStream_t sl = sides[(2 * c->learned_index) % 3], sf = sides[(2 * c->learned_index + 1) % 3];
     if (serial) {
         // after everything so far, and then the reject flags join the flags
-        TRY_HIP(c, hipEventRecord(c->ev_tail, c->stream), "event");
-        TRY_HIP(c, hipStreamWaitEvent(sl, c->ev_tail, 0), "stream wait");
-        TRY_HIP(c, hipStreamWaitEvent(sf, c->ev_tail, 0), "stream wait");
+        TRY_HIP(c, order_sides(c, {sl, sf}, capture), "stream wait");
     } else {
         // back to back, no reject flag is set: the fallback blend of every frame clears
         // those of its probes, and a frame with a rejected history is serial

@@ -1,0 +1,94 @@
+"""Order of a context's work on its streams: calls of every kind between frames that
+would otherwise overlap, against a context that never overlaps them."""
+import sys
+
+import numpy as np
+import pytest
+
+import scenegen
+
+pytestmark = pytest.mark.gpu
+
+
+def announce(msg):
+    print(f"[gpu] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+    from paper_2007_14394_amd import sdfddgi
+    assert torch.cuda.is_available(), "GPU tests need a visible gfx950 device"
+    sdfddgi.load_library()
+    return sdfddgi
+
+
+@pytest.fixture(scope="module")
+def scene():
+    return scenegen.config2(2, probes=8192, frames=20, rays=64, grid=64)
+
+
+def denoiser(S):
+    from paper_2007_14394_amd import denoiser_weights
+    net = denoiser_weights.load()
+    return S.sdfddgi_denoiser_create(net["params"], net["irr_scale"], net["depth_scale"])
+
+
+FORMS = {"plain": {}, "fp16": {}, "analytic": dict(analytic=True),
+         "learned": dict(learned_rays=16, fallback_error=0.05)}
+
+
+def context(S, w, form, **kw):
+    flags = (S.SDFDDGI_FLAG_FP16 if form == "fp16" else 0) | kw.pop("flags", 0)
+    return S.context_from_workload(w, flags=flags, **FORMS[form], **kw)
+
+
+# f: a frame; m: the maps read; b: Eq. 3 on a payload; e: training examples; r: relocation;
+# h: histories rejected. Two frames and more after each call, so that the frames take every
+# ray set and every side stream; for learned frames the calls come at both parities.
+SEQUENCES = {"plain": "ffbfmfmfbffmfrfmfmfhfmbfmffm", "fp16": "ffbfmfmfbffmfrfmfmfhfmbfmffm",
+             "analytic": "ffbfmfmfbffmfmfhfmbfmffm", "learned": "ffefmfmfmefmffmferfmfmfefmffm"}
+
+
+@pytest.mark.parametrize("form", SEQUENCES)
+def test_calls_between_overlapping_frames(S, scene, form):
+    import torch
+    announce(f"{form}: {SEQUENCES[form]}")
+    w, den, got = scene, denoiser(S), []
+    payload = torch.from_numpy(scenegen.random_payload(
+        w.num_probes, 64, seed=3, t_max=w.params.t_max)).to("cuda:0")
+    # work that keeps the caller's stream busy while the host goes on to the next calls
+    busy = torch.rand(6144, 6144, device="cuda:0")
+    for flags in (0, S.SDFDDGI_FLAG_RECORD_RAYS):   # (one that keeps records never overlaps)
+        ctx = context(S, w, form, flags=flags)
+        target = torch.zeros(ctx.irr_shape, device="cuda:0")
+        reads, frame = [], 0
+        for k, op in enumerate(SEQUENCES[form]):
+            if op in "ber":
+                torch.mm(busy, busy)
+            fr = w.frames[frame % len(w.frames)]
+            args = (fr.dir_to_light, fr.radiance_rgb, fr.rotation_seed)
+            if op == "f":
+                frame += 1
+                if form == "learned":
+                    S.sdfddgi_update_frame_learned(ctx, den, *args)
+                else:
+                    S.sdfddgi_update_frame(ctx, *args)
+            elif op == "m":
+                reads += [m.clone() for m in S.sdfddgi_get_maps(ctx)]
+            elif op == "b":
+                S.sdfddgi_blend(ctx, payload, 1000 + k)
+            elif op == "e":
+                reads += [t.clone() for t in S.sdfddgi_learned_examples(
+                    ctx, den, fr.dir_to_light, fr.radiance_rgb, 1000 + k, target, 0.05)]
+            elif op == "r":
+                S.sdfddgi_relocate_probes(ctx, 0.6, 0.25, 8, 0.1 + 0.01 * k)
+            else:
+                S.sdfddgi_reset_history(ctx)
+        torch.cuda.synchronize()
+        got.append(reads)
+        S.sdfddgi_destroy(ctx)
+    assert len(got[0]) == len(got[1]) > 0
+    for k, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), k
