@@ -210,7 +210,9 @@ sdfddgi_status sdfddgi_create_analytic(int32_t nprims, const int32_t *kind, cons
  * Consecutive calls with no other call on the context in between, except those
  * that only read the maps (sdfddgi_get_maps, sdfddgi_sample_irradiance), overlap
  * (see the stream convention above); the results are the same as one at a time.
- * A context created with SDFDDGI_FLAG_RECORD_RAYS never overlaps frames. */
+ * A context created with SDFDDGI_FLAG_RECORD_RAYS never overlaps frames, nor does
+ * one from the first call on that is recorded in a capture of its stream (the graph
+ * may be replayed between any later calls). */
 sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *ctx, const sdfddgi_light *light,
                                     uint64_t rotation_seed);
 

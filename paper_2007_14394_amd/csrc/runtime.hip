@@ -110,7 +110,6 @@ bool finite_all(const float *v, int n) {
 // rays (rays_per_probe) and the learned form's low ray count.
 struct RaySet {
     int R = 0, Rpad = 0;
-    bool captured = false;           // the done event was last recorded in a stream capture
     double *base = nullptr;          // [R][3] unrotated spherical-Fibonacci set
     float *dirs = nullptr, *norm_i = nullptr, *norm_d = nullptr;
     float *wt_i = nullptr, *wt_d = nullptr;   // weight tables [T][Rpad], or those of the
@@ -191,6 +190,9 @@ struct sdfddgi_ctx {
     hipStream_t side = nullptr;
     hipEvent_t ev_primary = nullptr, ev_tail = nullptr;
     bool serialize_next = true;
+    bool captured = false;       // some call was recorded in a stream capture: the graph may
+                                 // be replayed between any two calls, which no event here
+                                 // tells of, so from then on every frame is serial
     // Learned frames overlap among themselves; a switch between plain and learned
     // frames waits for everything before it. Learned frame n (parity k = n % 2, low
     // set lo = low[k]) has two side chains, dealt in turn to the three side streams
@@ -835,6 +837,15 @@ TraceArgs trace_pass(const TraceArgs &base, const RaySet &r, int *counters, int 
     return t;
 }
 
+// Whether the stream is being captured. (The null stream, which cannot be asked while some
+// other stream is, cannot be captured either.)
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // reads_maps: the call only reads the current maps, on the caller's stream. A frame's side
 // chains touch no map but those that its predecessor's work on that stream is done with, so
 // the next frame may overlap such a call as it may overlap the frame before.
@@ -847,26 +858,19 @@ sdfddgi_status check_ctx(sdfddgi_ctx *c, bool reads_maps = false) {
     if (!reads_maps) c->serialize_next = true;
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
+    c->captured = c->captured || capturing(c->stream);
     return SDFDDGI_OK;
 }
 
-// Whether the caller's stream is being captured (or cannot be asked): the frame then waits
-// for the stream's work so far, which draws the side streams into the capture.
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &status);
-    if (e != hipSuccess) (void)hipGetLastError();
-    return e != hipSuccess || status != hipStreamCaptureStatusNone;
-}
-
 // The start of a serial frame: `used`, the side streams that it launches on, after all
-// work on the caller's stream so far, and so the context's other side streams. (Those are
-// left out of a capture, which they would not join again.)
-hipError_t order_sides(sdfddgi_ctx *c, std::initializer_list<hipStream_t> used, bool capture) {
+// work on the caller's stream so far, and so the context's other side streams. (A context
+// that was captured uses no others, and a capture that they were drawn into would not be
+// joined by them again.)
+hipError_t order_sides(sdfddgi_ctx *c, std::initializer_list<hipStream_t> used) {
     hipError_t e = hipEventRecord(c->ev_tail, c->stream);
     for (hipStream_t s : {c->side, c->side2, c->side3}) {
         const bool in_use = std::find(used.begin(), used.end(), s) != used.end();
-        if (e == hipSuccess && s && (in_use || !capture)) e = hipStreamWaitEvent(s, c->ev_tail, 0);
+        if (e == hipSuccess && (in_use || !c->captured)) e = hipStreamWaitEvent(s, c->ev_tail, 0);
     }
     return e;
 }
@@ -1228,8 +1232,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     bool serial = !c || c->serialize_next || c->records || c->learned_chain;
     sdfddgi_status st = check_ctx(c);
     if (st != SDFDDGI_OK) return st;
-    const bool capture = capturing(c->stream);
-    serial = serial || capture || c->spare.captured;
+    serial = serial || c->captured;
     c->learned_chain = false;
     float l[3], rad[3];
     if ((st = light_of(c, light, l, rad)) != SDFDDGI_OK) return st;
@@ -1248,7 +1251,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     // done event; so wait for that (the trace then starts as soon as its set is
     // free), or, when serial, for everything enqueued so far
     if (serial) {
-        TRY_HIP(c, order_sides(c, {c->side}, capture), "stream wait");
+        TRY_HIP(c, order_sides(c, {c->side}), "stream wait");
     } else {
         TRY_HIP(c, hipStreamWaitEvent(c->side, r.done, 0), "stream wait");
     }
@@ -1305,7 +1308,6 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
     TRY_HIP(c, ev.mark(5), "event");
     TRY_HIP(c, ev.mark(10), "event");
     TRY_HIP(c, hipEventRecord(r.done, c->stream), "event");
-    r.captured = capture;
     frame_done(c, false);
     std::swap(c->main, c->spare);
     c->cur = nxt;
@@ -1615,8 +1617,7 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     bool serial = !c || c->serialize_next || c->records || !c->learned_chain;
     sdfddgi_status st = check_ctx(c);
     if (st != SDFDDGI_OK) return st;
-    const bool capture = capturing(c->stream);
-    serial = serial || capture || c->low[c->learned_index % 2].captured;
+    serial = serial || c->captured;
     c->learned_chain = false;
     if ((st = check_learned(c, d)) != SDFDDGI_OK) return st;
     float l[3], rad[3];
@@ -1629,7 +1630,7 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     hipStream_t sl = sides[(2 * c->learned_index) % 3], sf = sides[(2 * c->learned_index + 1) % 3];
     if (serial) {
         // after everything so far, and then the reject flags join the flags
-        TRY_HIP(c, order_sides(c, {sl, sf}, capture), "stream wait");
+        TRY_HIP(c, order_sides(c, {sl, sf}), "stream wait");
     } else {
         // back to back, no reject flag is set: the fallback blend of every frame clears
         // those of its probes, and a frame with a rejected history is serial
@@ -1686,7 +1687,8 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     TRY_HIP(c, launch_hits(tf, gf, sf), "launching hits_kernel");
     TRY_HIP(c, launch_tables_weights(taf, sf), "launching tables_kernel");
     TRY_HIP(c, ev.mark_on(8, sf), "event");
-    TRY_HIP(c, hipStreamWaitEvent(sf, c->ev_end, 0), "stream wait");
+    if (!serial)   // (a serial frame's streams are behind it as it is)
+        TRY_HIP(c, hipStreamWaitEvent(sf, c->ev_end, 0), "stream wait");
     TRY_HIP(c, ev.mark_on(11, sf), "event");
     TRY_HIP(c, launch_shade(tf, sf), "launching shade_kernel");
     TRY_HIP(c, launch_blend(blend_args(c, fb, fb.payload, c->prm.hysteresis, c->irr[c->cur],
@@ -1733,7 +1735,6 @@ sdfddgi_status sdfddgi_update_frame_learned(sdfddgi_ctx *c, const sdfddgi_denois
     TRY_HIP(c, hipEventRecord(fb.done, c->stream), "event");
     TRY_HIP(c, ev.mark(10), "event");
     TRY_HIP(c, hipEventRecord(c->ev_end, c->stream), "event");
-    lo.captured = capture;
     ++c->learned_index;
     frame_done(c, true);
     c->last_learned = k;

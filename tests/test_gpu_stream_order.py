@@ -92,3 +92,58 @@ def test_calls_between_overlapping_frames(S, scene, form):
     assert len(got[0]) == len(got[1]) > 0
     for k, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), k
+
+
+# Two frames and their maps read, captured once and replayed between frames that the caller
+# runs directly (in pairs, as the graph reads and writes fixed map buffers).
+@pytest.mark.parametrize("form", FORMS)
+def test_frames_around_captured_ones(S, scene, form):
+    import torch
+    announce(f"{form}: captured frames")
+    w, den, got = scene, denoiser(S), []
+    busy = torch.rand(6144, 6144, device="cuda:0")
+    for capture in (True, False):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            ctx = context(S, w, form, flags=0 if capture else S.SDFDDGI_FLAG_RECORD_RAYS)
+            bufs = [(torch.zeros(ctx.irr_shape, device="cuda:0"),
+                     torch.zeros(ctx.depth_shape, device="cuda:0")) for _ in range(2)]
+            reads = []
+
+            def frame(k):
+                fr = w.frames[k]
+                args = (fr.dir_to_light, fr.radiance_rgb, fr.rotation_seed)
+                if form == "learned":
+                    S.sdfddgi_update_frame_learned(ctx, den, *args)
+                else:
+                    S.sdfddgi_update_frame(ctx, *args)
+
+            def pair():
+                for k, (irr, dep) in enumerate(bufs):
+                    frame(2 + k)
+                    S.sdfddgi_get_maps(ctx, irr, dep)
+
+            frame(0)
+            frame(1)
+            graph = torch.cuda.CUDAGraph()
+            if capture:
+                with torch.cuda.graph(graph, stream=stream):
+                    pair()
+            for k, op in enumerate("!ffmfmfm!mfmfmffm!!ffmfmfm!"):
+                if op == "!":
+                    torch.mm(busy, busy)   # the replay waits while the host goes on
+                    if capture:
+                        graph.replay()
+                    else:
+                        pair()
+                    reads += [m.clone() for pair_of in bufs for m in pair_of]
+                elif op == "f":
+                    frame(4 + k % 16)
+                else:
+                    reads += [m.clone() for m in S.sdfddgi_get_maps(ctx)]
+            torch.cuda.synchronize()
+            got.append(reads)
+            S.sdfddgi_destroy(ctx)
+    assert len(got[0]) == len(got[1]) > 0
+    for k, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), k
