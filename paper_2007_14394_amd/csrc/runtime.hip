@@ -862,6 +862,31 @@ sdfddgi_status check_ctx(sdfddgi_ctx *c, bool reads_maps = false) {
     return SDFDDGI_OK;
 }
 
+// Whether p is memory of the given device.
+bool memory_of(int device, const void *p) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) == hipSuccess)
+        return a.type == hipMemoryTypeDevice && a.device == device;
+    (void)hipGetLastError();
+    return false;
+}
+
+// A pair of maps to the caller's buffers (either may be null): one launch where both are the
+// device's own memory; what a kernel may not reach, such as another device's, by copies.
+hipError_t copy_maps(int device, float *irr, const float *from_irr, int64_t n_irr, float *depth,
+                     const float *from_depth, int64_t n_depth, hipStream_t stream) {
+    if (!irr) n_irr = 0;
+    if (!depth) n_depth = 0;
+    if ((!irr || memory_of(device, irr)) && (!depth || memory_of(device, depth)))
+        return launch_copy_pair(irr, from_irr, n_irr, depth, from_depth, n_depth, stream);
+    hipError_t e = hipSuccess;
+    if (irr)
+        e = hipMemcpyAsync(irr, from_irr, n_irr * sizeof(float), hipMemcpyDefault, stream);
+    if (e == hipSuccess && depth)
+        e = hipMemcpyAsync(depth, from_depth, n_depth * sizeof(float), hipMemcpyDefault, stream);
+    return e;
+}
+
 // The start of a serial frame: `used`, the side streams that it launches on, after all
 // work on the caller's stream so far, and so the context's other side streams. (A context
 // that was captured uses no others, and a capture that they were drawn into would not be
@@ -1355,8 +1380,8 @@ sdfddgi_status sdfddgi_sample_irradiance(sdfddgi_ctx *c, const float *points,
 sdfddgi_status sdfddgi_get_maps(sdfddgi_ctx *c, float *irr, float *depth) {
     sdfddgi_status st = check_ctx(c, true);
     if (st != SDFDDGI_OK) return st;
-    TRY_HIP(c, launch_copy_pair(irr, c->irr[c->cur], irr ? c->irr_floats : 0, depth,
-                                c->depth[c->cur], depth ? c->depth_floats : 0, c->stream),
+    TRY_HIP(c, copy_maps(c->device, irr, c->irr[c->cur], c->irr_floats, depth, c->depth[c->cur],
+                         c->depth_floats, c->stream),
             "copying the atlases");
     return SDFDDGI_OK;
 }
@@ -2895,10 +2920,8 @@ sdfddgi_status sdfddgi_batch_get_maps(sdfddgi_batch *b, int32_t scene, float *ir
     const size_t ti = 10 * 10 * 3, td = 18 * 18 * 2;
     hipError_t e = hipSetDevice(b->device);
     if (e != hipSuccess) return lhip_fail(e, "hipSetDevice");
-    e = launch_copy_pair(irr, b->irr[b->cur] + (size_t)d.probe_base * ti,
-                         irr ? d.P * (int64_t)ti : 0, depth,
-                         b->depth[b->cur] + (size_t)d.probe_base * td,
-                         depth ? d.P * (int64_t)td : 0, b->stream);
+    e = copy_maps(b->device, irr, b->irr[b->cur] + (size_t)d.probe_base * ti, d.P * (int64_t)ti,
+                  depth, b->depth[b->cur] + (size_t)d.probe_base * td, d.P * (int64_t)td, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return lhip_fail(e, "copying maps");
     return SDFDDGI_OK;

@@ -147,3 +147,42 @@ def test_frames_around_captured_ones(S, scene, form):
     assert len(got[0]) == len(got[1]) > 0
     for k, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), k
+
+
+# Maps read into memory that no kernel of the device may write (here the host's) are copied
+# as into the device's own.
+@pytest.mark.parametrize("batch", [False, True])
+def test_maps_read_into_other_memory(S, batch):
+    import ctypes
+    import torch
+    announce(f"maps to the host, batch={batch}")
+    lib = S.load_library()
+    if batch:
+        specs, seeds = scenegen.batch_scene_specs(1, 2, frames=1, sdf_range=(20, 24),
+                                                  probes_xz=(2, 4), probes_y=(2, 3), rays=(64, 64))
+        h = S.batch_from_specs(specs)
+        S.sdfddgi_batch_update_frame(h, [(sp.frames[0].dir_to_light, sp.frames[0].radiance_rgb)
+                                         for sp in specs], seeds[0])
+        ref = [m.cpu().numpy() for m in S.sdfddgi_batch_get_maps(h, 1)]
+        read = lambda irr, dep: lib.sdfddgi_batch_get_maps(h.handle, 1, irr, dep)
+    else:
+        w = scenegen.small_cascade(2, probes=(3, 5, 3), rays=64)
+        h = S.context_from_workload(w)
+        fr = w.frames[0]
+        S.sdfddgi_update_frame(h, fr.dir_to_light, fr.radiance_rgb, fr.rotation_seed)
+        ref = [m.cpu().numpy() for m in S.sdfddgi_get_maps(h)]
+        read = lambda irr, dep: lib.sdfddgi_get_maps(h.handle, irr, dep)
+    for which in ((0, 1), (0,), (1,)):
+        host = [np.full(m.size + 2, -1.0, np.float32) for m in ref]
+        ptr = [ctypes.c_void_p(m.ctypes.data + 4) if k in which else None
+               for k, m in enumerate(host)]
+        assert read(*ptr) == S.SDFDDGI_OK
+        torch.cuda.synchronize()
+        for k, (m, r) in enumerate(zip(host, ref)):
+            assert np.array_equal(m[1:-1], r.ravel()) if k in which else (m == -1.0).all()
+            assert m[0] == m[-1] == -1.0
+        # one to the host, one to the device
+        mixed = torch.full(ref[1].shape, -1.0, device="cuda:0")
+        assert read(ptr[0], ctypes.c_void_p(mixed.data_ptr())) == S.SDFDDGI_OK
+        torch.cuda.synchronize()
+        assert np.array_equal(mixed.cpu().numpy(), ref[1])
