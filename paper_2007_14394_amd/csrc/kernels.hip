@@ -15,6 +15,7 @@
 // one fixed binary32 operation sequence, spelled out with fmaf; contraction of
 // any other multiply-add is disabled for this file.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 #include "octahedral.h"
@@ -78,10 +79,12 @@ __device__ __forceinline__ void load_sdf(const TraceArgs &a, SdfLds<kSdf> &s) {
 
 // Kernel arguments that only rare branches of a trace loop need, read where they are
 // used: hoisted out of the loop like other uniform values they would take the scalar
-// registers that every sample's level bounds need. The struct is the kernel's only
-// argument, at the start of its argument segment.
+// registers that every sample's level bounds need. The struct has to be the only argument
+// of the calling kernel, whose type `Kernel` is: it then starts the argument segment.
 typedef const __attribute__((address_space(4))) TraceArgs RareArgs;
+template <typename Kernel>
 __device__ __forceinline__ RareArgs *rare_args() {
+    static_assert(std::is_same_v<Kernel, void(TraceArgs)>, "not this kernel's argument");
     RareArgs *p = (RareArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return p;
@@ -206,9 +209,8 @@ __device__ __forceinline__ float4 shade_hit(const TraceArgs &a, float3 alb, floa
 
 // Per-wave staging of hit-queue entries (ray, bits of t, packed info, 0) in LDS;
 // flushed to the global queue 64 at a time with one atomic.
-__device__ __forceinline__ void flush_hits(int4 *buf, int count) {
+__device__ __forceinline__ void flush_hits(RareArgs &a, int4 *buf, int count) {
     if (count == 0) return;
-    RareArgs &a = *rare_args();
     int base = 0;
     if (__lane_id() == 0) base = atomicAdd(a.counter + 2, count);
     base = __builtin_amdgcn_readfirstlane(base);
@@ -250,6 +252,7 @@ constexpr int kFetchAt = 48;      // a wave fetches 64 more rays when no more th
 // (478 / 419 us) were no faster.
 template <int kSdf, bool kWide = false>
 __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
+    using Self = decltype(primary_kernel<kSdf, kWide>);
     __shared__ SdfLds<kSdf> s_sdf;
     __shared__ int4 s_hits[4][64];
     constexpr int kRayQueue = 128;
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
     int2 n_first = make_int2(0, -1);
     while (true) {
         if (stage == 2) {
-            RareArgs &f = *rare_args();
+            RareArgs &f = *rare_args<Self>();
             if (lane < coming) {
                 // the first sample sits at the probe (fma(0, w, o) = o) for every
                 // ray of it: where that sample only steps on (a level holds the
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
             waiting += coming;
             stage = 0;
         } else if (stage == 1) {
-            RareArgs &f = *rare_args();
+            RareArgs &f = *rare_args<Self>();
             if (lane < coming) {
                 m0 = f.probe_pos[3 * n_probe];
                 m1 = f.probe_pos[3 * n_probe + 1];
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
         }
         if (__popcll(live) <= 64 - kEndBatch) {
             if (ended) {
-                RareArgs &f = *rare_args();
+                RareArgs &f = *rare_args<Self>();
                 bool hit = false;
                 int4 entry = make_int4(0, 0, 0, 0);
                 if (in_mask(ended)) {
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
                 if (hm) {
                     const int n = __popcll(hm);
                     if (staged + n > 64) {
-                        flush_hits(s_hits[wave], staged);
+                        flush_hits(*rare_args<Self>(), s_hits[wave], staged);
                         staged = 0;
                     }
                     if (hit) s_hits[wave][staged + __popcll(hm & below)] = entry;
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
             }
             if (stage == 0 && !feed.exhausted &&
                 (plenty ? waiting <= kFetchAt : __popcll(live) <= 32)) {
-                RareArgs &f = *rare_args();
+                RareArgs &f = *rare_args<Self>();
                 coming = 0;
                 while (coming < 64 && !feed.exhausted) {
                     int first = 0;
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
             }
             if (!live) {  // then no ray waits either
                 if (stage == 0 && feed.exhausted) {
-                    flush_hits(s_hits[wave], staged);
+                    flush_hits(*rare_args<Self>(), s_hits[wave], staged);
                     break;
                 }
                 continue;
@@ -408,6 +411,7 @@ __global__ __launch_bounds__(256) void primary_kernel(TraceArgs a) {
 // whichever lanes were due, beside the stepping ones, 202 and 216 us at 42 % of the lanes.
 template <int kSdf, bool kWide = false>
 __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
+    using Self = decltype(hits_kernel<kSdf, kWide>);
     constexpr int kQueue = 128;
     __shared__ SdfLds<kSdf> s_sdf;
     __shared__ float4 s_rays[4][kQueue];   // origin, hit-queue index
@@ -429,7 +433,7 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
     float p0 = 0, p1 = 0, p2 = 0, w0 = 0, w1 = 0, w2 = 0;
     while (true) {
         if (stage == 2) {
-            RareArgs &f = *rare_args();
+            RareArgs &f = *rare_args<Self>();
             bool lit = false;
             float4 from = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (lane < coming) {
@@ -463,7 +467,7 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
             waiting += __popcll(m);
             stage = 0;
         } else if (stage == 1) {
-            RareArgs &f = *rare_args();
+            RareArgs &f = *rare_args<Self>();
             if (lane < coming) {
                 const int p = e.x / f.R, i = e.x - p * f.R;
                 p0 = f.probe_pos[3 * p]; p1 = f.probe_pos[3 * p + 1]; p2 = f.probe_pos[3 * p + 2];
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
             stage = 2;
         }
         if (__popcll(live) <= 64 - kEndBatch) {
-            RareArgs &f = *rare_args();
+            RareArgs &f = *rare_args<Self>();
             if (ended) {
                 if (in_mask(ended)) {
                     int steps;
