@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256) void batch_hits_kernel(BatchArgs a, int chunk)
                 s_rays[wave][at] = from;
                 s_ray_sc[wave][at] = e.w;
             }
-            __builtin_amdgcn_wave_barrier();
+            order_wave_stores();   // the records; a lane of a blocked ray changes another's
             waiting += __popcll(m);
             stage = 0;
         } else if (stage == 1) {

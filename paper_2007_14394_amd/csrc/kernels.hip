@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) void hits_kernel(TraceArgs a) {
             }
             const uint64_t m = __ballot(lit);
             if (lit) s_rays[wave][(head + waiting + __popcll(m & below)) & (kQueue - 1)] = from;
-            __builtin_amdgcn_wave_barrier();
+            order_wave_stores();   // the records; a lane of a blocked ray changes another's
             waiting += __popcll(m);
             stage = 0;
         } else if (stage == 1) {

@@ -294,6 +294,14 @@ struct Feeder {
     }
 };
 
+// Whatever lanes of the wave store before this point reaches memory before what others of
+// its lanes store after it. The memory model gives a wave's operations in the order of the
+// program, so the fence is for the compiler and no instruction.
+__device__ __forceinline__ void order_wave_stores() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Whether the calling lane is in a wave-uniform mask.
 __device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
