@@ -126,12 +126,15 @@ __global__ __launch_bounds__(256) void candidate_cells_kernel(AnalyticScene a, u
     const float q0 = fmaf((float)(lane & 3) + 0.5f, quarter, x0);
     const float q1 = fmaf((float)((lane >> 2) & 3) + 0.5f, quarter, x1);
     const float q2 = fmaf((float)(lane >> 4) + 0.5f, quarter, x2);
+    float nearest = INFINITY;
+    int at = -1;
+    for (int j = 0; j < count; ++j) {
+        const float d = prim_distance(a.prims[list[j]], q0, q1, q2);
+        if (d < nearest) { nearest = d; at = list[j]; }
+    }
     Slope b;
     b.d = INFINITY; b.out = 0.0f; b.g0 = b.g1 = b.g2 = 0.0f;
-    for (int j = 0; j < count; ++j) {
-        const Slope s = slope_at(a.prims[list[j]], q0, q1, q2);
-        if (s.d < b.d) b = s;
-    }
+    if (at >= 0) b = slope_at(a.prims[at], q0, q1, q2);
     int n = 0;
     uint32_t entry = 0;
     for (int j = 0; j < count; ++j) {
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(256) void candidate_cells_kernel(AnalyticScene a, u
         // (not "<=": what is undefined stays listed)
         if (!__ballot(!(s.d > b.d + (L * rp + slack)))) continue;
         if (lane == n) entry = 32u * (uint32_t)m;
-        ++n;
+        if (++n > kCellPrims) break;   // (the cell walks the clusters)
     }
     entry = __shfl(entry, min(lane, max(min(n, kCellPrims) - 1, 0)));
     if (lane == 0) entry |= (n > 8 ? 1u : 0u) | (n > kCellPrims || n == 0 ? 2u : 0u);
