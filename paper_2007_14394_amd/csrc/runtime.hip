@@ -2281,8 +2281,8 @@ BatchArgs batch_args(const sdfddgi_batch *b, int cur, int lane) {
 // lane `lane`'s buffers (a frame normally uses lane cur), in two parts: the front
 // (counters, tables, primary trace and the first half of the hit shading; reads no map)
 // and the back (lookups, blend). `ev` (may be null) receives events before and after the
-// primary trace and after the hit shading (front), and (when ev[3] is set) after the
-// blend (back).
+// primary trace and after the hit shading (front: 0, 1, 2), and before and after the blend
+// (back: 3, 4).
 hipError_t batch_enqueue_front(sdfddgi_batch *b, int lane, const BatchTuning &t, hipStream_t st,
                                hipEvent_t *ev) {
     const int cur = lane;
@@ -2319,6 +2319,7 @@ hipError_t batch_enqueue_front(sdfddgi_batch *b, int lane, const BatchTuning &t,
 hipError_t batch_enqueue_back(sdfddgi_batch *b, int cur, int lane, const BatchTuning &t,
                               hipStream_t st, hipEvent_t *ev) {
     hipError_t e = launch_batch_shade(batch_args(b, cur, lane), st);
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[3], st);
     if (e != hipSuccess) return e;
     BatchBlendArgs bb{};
     bb.nscenes = b->S;
@@ -2332,7 +2333,7 @@ hipError_t batch_enqueue_back(sdfddgi_batch *b, int cur, int lane, const BatchTu
     bb.reject = b->reject;
     bb.done = b->stamps[lane] + 1;
     if ((e = launch_batch_blend(bb, b->nblocks, t, st)) != hipSuccess) return e;
-    return ev && ev[3] ? hipEventRecord(ev[3], st) : hipSuccess;
+    return ev ? hipEventRecord(ev[4], st) : hipSuccess;
 }
 
 // One whole frame on the caller's stream (the autotuner's candidates).
@@ -2779,24 +2780,24 @@ sdfddgi_status sdfddgi_batch_autotune(sdfddgi_batch *b, const sdfddgi_light *lig
     uint8_t *saved = nullptr;
     if ((e = dev_alloc(&saved, (size_t)b->GP)) != hipSuccess) return lhip_fail(e, "allocating");
     e = hipMemcpyAsync(saved, b->reject, (size_t)b->GP, hipMemcpyDeviceToDevice, b->stream);
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-    for (int k = 0; k < 4 && e == hipSuccess; ++k) e = hipEventCreate(&ev[k]);
+    hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    for (int k = 0; k < 5 && e == hipSuccess; ++k) e = hipEventCreate(&ev[k]);
     const int pmax = batch_resident_blocks(b->device, false);
     const int hmax = batch_resident_blocks(b->device, true);
     int count = 0;
-    // time one configuration: mean primary, hit shading and blend kernel times over
-    // `frames`
+    // time one configuration: mean times of the primary trace, the first half of the hit
+    // shading and the blend over `frames`
     float blend = 0.0f;
     auto measure = [&](const BatchTuning &t, float &prim, float &hits) -> hipError_t {
         prim = hits = blend = 0.0f;
         for (int f = 0; f < frames; ++f) {
             hipError_t x = batch_enqueue(b, b->cur, t, ev);
             if (x != hipSuccess) return x;
-            if ((x = hipEventSynchronize(ev[3])) != hipSuccess) return x;
+            if ((x = hipEventSynchronize(ev[4])) != hipSuccess) return x;
             float a = 0.0f, c = 0.0f, d = 0.0f;
             if ((x = hipEventElapsedTime(&a, ev[0], ev[1])) != hipSuccess) return x;
             if ((x = hipEventElapsedTime(&c, ev[1], ev[2])) != hipSuccess) return x;
-            if ((x = hipEventElapsedTime(&d, ev[2], ev[3])) != hipSuccess) return x;
+            if ((x = hipEventElapsedTime(&d, ev[3], ev[4])) != hipSuccess) return x;
             prim += a / frames;
             hits += c / frames;
             blend += d / frames;
@@ -2896,7 +2897,7 @@ sdfddgi_status sdfddgi_batch_autotune(sdfddgi_batch *b, const sdfddgi_light *lig
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->reject, saved, (size_t)b->GP, hipMemcpyDeviceToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < 5; ++k)
         if (ev[k]) (void)hipEventDestroy(ev[k]);
     dev_free(saved);
     if (e != hipSuccess) return lhip_fail(e, "autotuning");
