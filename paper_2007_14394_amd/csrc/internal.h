@@ -76,9 +76,14 @@ struct AnalyticPrim {
 constexpr int kCellPrims = 16;
 constexpr int kMaxCellLevels = 16;
 constexpr int kCellMargin = 8;
-// Cells of level 0, about. At 400 primitives and 16384 x 64 rays a frame takes 505, 523, 510,
-// 477, 530, 530 us with 2^14 .. 2^19: fewer candidates a cell against more lines. Listing them
-// takes 1.2 ms of the context's creation with 2^16 and 2.0 with 2^18.
+// Cells of level 0, about: fewer candidates a cell against more lines. With 2^14 .. 2^19 a
+// frame of 16384 x 64 rays in the open, maps read back, takes (us, runs within 1 %):
+//     24 primitives   209   210   209   210   213   215
+//    100              235   232   233   233   236   240
+//    400              417   444   430   410   449   445
+//   1024             1317  1413  1357  1290  1511  1443
+// -- flat where primitives are few; where they are many, up and down by more than the runs
+// differ (for reasons not looked into), and best with 2^17 at both counts.
 constexpr int kCandidateCells = 1 << 17;
 struct AnalyticScene {
     const AnalyticPrim *prims;       // [nprims], ordered by cluster

@@ -10,8 +10,9 @@
 //   examples_kernel   training pairs: features and targets (a converged atlas) per texel
 //   infer_kernel      the network on a feature array
 //   train_kernel      loss gradient over a minibatch (forward, backward, weight
-//                     gradients; all contractions on bfloat16 MFMA)
-//   adam_kernel       Adam update of the binary32 masters
+//                     gradients; all contractions on bfloat16 MFMA), one sum per workgroup
+//   update_kernel     those sums added up, Adam's step on the binary32 masters, and the
+//                     new weights into the packs
 //
 // MFMA layout (v_mfma_f32_16x16x32_bf16, wave64): lane l = n + 16 g holds the A
 // operand A[n][8g .. 8g+7], the B operand B[8g .. 8g+7][n], and the result

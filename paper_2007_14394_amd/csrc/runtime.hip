@@ -112,8 +112,8 @@ struct RaySet {
     int R = 0, Rpad = 0;
     double *base = nullptr;          // [R][3] unrotated spherical-Fibonacci set
     float *dirs = nullptr, *norm_i = nullptr, *norm_d = nullptr;
-    float *wt_i = nullptr, *wt_d = nullptr;   // weight tables [T][Rpad], or those of the
-    _Float16 *w16_i = nullptr;       // precision form
+    float *wt_i = nullptr, *wt_d = nullptr;   // weight tables in the blend's operand order
+    _Float16 *w16_i = nullptr;       // (weight_index), or those of the precision form
     __bf16 *w16_d = nullptr;
     float4 *payload = nullptr;       // [P][R]
     int4 *hitq = nullptr;            // [P][R]
@@ -186,7 +186,8 @@ struct sdfddgi_ctx {
     // the next frame wait for everything before it (serialize_next), on every side
     // stream, also those that only later frames use: what such a call touched (a set's
     // tables, the probes' positions) no set's event tells of. A small room read
-    // back after every frame: 191 -> 126 us a frame.
+    // back after every frame: 191 -> 126 us a frame where frames follow one another (one
+    // frame alone, with nothing to overlap, gains nothing from it).
     hipStream_t side = nullptr;
     hipEvent_t ev_primary = nullptr, ev_tail = nullptr;
     bool serialize_next = true;
@@ -1266,10 +1267,14 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
                                    nullptr, nullptr, c->records);
     FrameEvents ev = frame_events(c);
     const int nxt = 1 - c->cur;
-    // Split hit shading when pipelined on a grid: the atlas-independent half on side2
+    // When pipelined on a grid, the atlas-independent half of the hit shading on side2
     // right after the trace, only the lookups behind the previous frame's blend
     // (16384 x 256, ms per frame, FP32 / FP16: 0.7275 / 0.590 unsplit, 0.719 /
-    // 0.576 split; that half's grid halved 0.736, not overlapped 0.734 in FP32)
+    // 0.576 split; that half's grid halved 0.736, not overlapped 0.734 in FP32). Analytic
+    // contexts run both halves on the caller's stream: their half depends on no atlas
+    // either, but so far the split was only measured (16384 x 64, maps read after every
+    // frame, us: 24 primitives 210 so and 193 split, 100: 233 and 227, 400: 410 and 405,
+    // 1024: 1290 and 1000; a frame alone 332 and 343 with 100)
     const bool split = !serial && !c->analytic;
     // side stream: tables and primary trace. This set was last used by the frame
     // before the previous one, whose hit shading and blend ran before that set's
@@ -1316,8 +1321,7 @@ sdfddgi_status sdfddgi_update_frame(sdfddgi_ctx *c, const sdfddgi_light *light,
         TRY_HIP(c, hipEventRecord(r.ready, c->side2), "event");
         TRY_HIP(c, hipStreamWaitEvent(c->stream, r.ready, 0), "stream wait");
     } else {
-        // caller's stream: hit shading (reads the previous atlas, so after the
-        // previous frame's blend)
+        // caller's stream: both halves of the hit shading
         TRY_HIP(c, hipStreamWaitEvent(c->stream, c->ev_primary, 0), "stream wait");
         TRY_HIP(c, ev.mark(3), "event");
         TRY_HIP(c, launch_hits(t, g, c->stream), "launching hits_kernel");

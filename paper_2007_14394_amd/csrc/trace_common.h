@@ -247,7 +247,7 @@ __device__ __forceinline__ float3 interp_irradiance(const float *__restrict__ at
     // four probes per iteration: 48 values in flight, half the registers of a full unroll.
     // Addresses of the probes from one lane address and uniform strides, and fused
     // multiply-adds: half the vector instructions. Samples of a coherent image (2 M points) are
-    // bound by the L1, one lookup a cycle (43 us, 45 before); the hit shading of 24 scenes,
+    // bound by the L1's lookups (43 us, 45 before); the hit shading of 24 scenes,
     // which shares the CUs with other kernels, gains more (6.80 -> 6.66 ms for four frames).
 #pragma unroll 4
     for (int c8 = 0; c8 < 8; ++c8) {
