@@ -1,6 +1,6 @@
 """Grids that the trace's 24-bit products and 32-bit offsets do not cover: far along an axis
 of more than 65536 vertices, and past 4 GiB of bricks. The single-scene trace and relocation
-against the reference checker, the batched form against single-scene contexts."""
+against the oracle, the batched form against single-scene contexts."""
 import sys
 
 import numpy as np
